@@ -13,11 +13,8 @@
 //                  comes from the M x M dual system (push-through identity):
 //                    S = Om (1 1^T + K) Om + lambda I,  Om = diag(sqrt(w)),  K_ij = D_i . D_j,
 //                    c = Om S^{-1} Om Y_{k+1},  alpha = sum_j c_j,  alpha_x = sum_j c_j D_j.
-//                  S, bordered by the right-hand side Om Y as an extra row, is factored in
-//                  registers. Each lane holds a block-cyclic set of lower-triangle entries. Each
-//                  pivot column is broadcast through LDS, one barrier per column with two column
-//                  buffers. The bordered row comes out as L^{-1} Om Y, so the forward solve is free,
-//                  and a back substitution gives S^{-1} Om Y. The nonlinearity needs only
+//                  S, bordered by the right-hand side Om Y as an extra column, is factored and solved
+//                  in registers on the FP64 matrix cores (fbsde_spd.hpp). The nonlinearity needs only
 //                  |Z|^2 = s^2 c^T K c and sum_i Z_i = s^2 sum_j c_j (rho_j - rho_m) (Z = s alpha_x).
 //                  Both come from G without forming alpha_x. Newton (eq. NRiter) on
 //                  y - Ybar - dt f(y, Z) then gives Y^m_k.
@@ -30,6 +27,7 @@
 #include <cmath>
 
 #include "fbsde_host.hpp"
+#include "fbsde_spd.hpp"
 
 namespace {
 
@@ -297,291 +295,105 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
     return s;
 }
 
-// Slot layout of the anchor system on an RI x RJ lane grid: row block a < A holds rows RI a .. RI a + RI - 1
-// and meets the lower triangle in the column blocks b <= bmax(a).
-template <int RI, int RJ>
-constexpr int bmax(int a) { return (RI * a + RI - 1) / RJ; }
-template <int RI, int RJ>
-constexpr int amin(int b) {    // first row block that meets column block b
-    int a = 0;
-    while (bmax<RI, RJ>(a) < b) ++a;
-    return a;
-}
-template <int RI, int RJ>
-constexpr int slot0(int a) {   // first slot of row block a
-    int e = 0;
-    for (int q = 0; q < a; ++q) e += bmax<RI, RJ>(q) + 1;
-    return e;
-}
-
-// 1 / x from the hardware reciprocal refined by two Newton steps r <- r + r (1 - x r) (each step squares
-// the relative error), to the last bits of the quotient: shorter than the IEEE division sequence on the
-// per-column critical path.
-__device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return r;
-}
-
-// One elimination step with the pivot in column block JB (a compile-time constant, so that only the
-// slots of blocks JB.. are touched: blocks left of the pivot are finished).  Writes the lanes' share of
-// pivot column jp into cb, waits at the barrier, then updates S_ij -= S_i,jp S_j,jp / S_jp,jp for
-// j > jp (in block JB only lanes right of the pivot).  Returns the pivot S_jp,jp.
-template <int RI, int RJ, int A, bool CACHE, int JB, int E>
-__device__ __forceinline__ double elim_step(double (&v)[E], double* cb, int jp, int tr, int tc) {
-    constexpr int B = bmax<RI, RJ>(A - 1) + 1;
-    const int jr = jp - RJ * JB;
-    if (tc == jr) {
-#pragma unroll
-        for (int a = amin<RI, RJ>(JB); a < A; ++a) cb[tr + RI * a] = v[slot0<RI, RJ>(a) + JB];
-    }
-    __syncthreads();
-    const double dj = cb[jp];
-    const double inv = recip(dj);
-    const bool right = tc > jr;
-    if constexpr (CACHE) {
-        double ci[A], cj[B];
-#pragma unroll
-        for (int a = amin<RI, RJ>(JB); a < A; ++a) ci[a] = cb[tr + RI * a];
-#pragma unroll
-        for (int b = JB; b < B; ++b) cj[b] = cb[tc + RJ * b] * inv;
-#pragma unroll
-        for (int a = amin<RI, RJ>(JB); a < A; ++a)
-#pragma unroll
-            for (int b = JB; b <= bmax<RI, RJ>(a); ++b) {
-                double& x = v[slot0<RI, RJ>(a) + b];
-                const double y = fma(-ci[a], cj[b], x);
-                x = (b > JB || right) ? y : x;
-            }
-    } else {
-#pragma unroll
-        for (int a = amin<RI, RJ>(JB); a < A; ++a)
-#pragma unroll
-            for (int b = JB; b <= bmax<RI, RJ>(a); ++b) {
-                double& x = v[slot0<RI, RJ>(a) + b];
-                const double y = fma(-cb[tr + RI * a], cb[tc + RJ * b] * inv, x);
-                x = (b > JB || right) ? y : x;
-            }
-    }
-    return dj;
-}
-
-// Calls elim_step with the runtime column block jb as a compile-time constant (a chain of uniform tests).
-template <int RI, int RJ, int A, bool CACHE, int JB, int E>
-__device__ __forceinline__ double elim_dispatch(int jb, double (&v)[E], double* cb, int jp, int tr, int tc) {
-    constexpr int B = bmax<RI, RJ>(A - 1) + 1;
-    if constexpr (JB + 1 < B) {
-        if (jb == JB) return elim_step<RI, RJ, A, CACHE, JB>(v, cb, jp, tr, tc);
-        return elim_dispatch<RI, RJ, A, CACHE, JB + 1>(jb, v, cb, jp, tr, tc);
-    } else {
-        return elim_step<RI, RJ, A, CACHE, JB>(v, cb, jp, tr, tc);
-    }
-}
-
-// One back-substitution step for row jp in row block IB (compile-time, so that only that block's slots
-// are touched): the lanes holding row jp take rr_j -= u_jp,j ct_jp for j < jp.
-template <int RI, int RJ, int IB, int E>
-__device__ __forceinline__ void bsub_step(const double (&v)[E], double* rr, int jp, int tr, int tc, double cj) {
-    if (tr == jp - RI * IB) {
-#pragma unroll
-        for (int b = 0; b <= bmax<RI, RJ>(IB); ++b) {
-            const int j = tc + RJ * b;
-            if (j < jp) rr[j] -= v[slot0<RI, RJ>(IB) + b] * cj;
-        }
-    }
-}
-template <int RI, int RJ, int A, int IB, int E>
-__device__ __forceinline__ void bsub_dispatch(int ib, const double (&v)[E], double* rr, int jp, int tr, int tc,
-                                              double cj) {
-    if constexpr (IB + 1 < A) {
-        if (ib == IB) return bsub_step<RI, RJ, IB>(v, rr, jp, tr, tc, cj);
-        return bsub_dispatch<RI, RJ, A, IB + 1>(ib, v, rr, jp, tr, tc, cj);
-    } else {
-        return bsub_step<RI, RJ, IB>(v, rr, jp, tr, tc, cj);
-    }
-}
-
-// One anchor m of point p at level k.  Grid (M, P), RI x RJ threads.  The bordered (M + 1) x (M + 1)
-// system (row M holds the right-hand side) is spread block-cyclically: lane (r, c) = (tid / RJ, tid % RJ)
-// owns the entries (r + RI a, c + RJ b), b <= bmax(a), a < A.  So every index is the lane's coordinate
-// plus a compile-time offset, and only the values take registers.
+// One anchor m of point p at level k.  Grid (M, P), NW wavefronts.  The M x M dual system, bordered by its
+// right-hand side, is built, factored and solved in registers as T x T tiles of the FP64 matrix cores
+// (SpdSystem in fbsde_spd.hpp).  Bound by the chain of the elimination steps and by instruction issue, not by
+// the matrix cores (64 points, per level, against an L D L^T in registers that broadcast one column a step
+// through LDS: M = 20 26 -> 16 us, M = 50 74 -> 77 us, M = 64 0.21 -> 0.14 ms, M = 100 0.69 -> 0.39 ms, M = 128
+// 1.8 -> 0.82 ms, M = 160 7.4 -> 1.8 ms, M = 200 11.2 -> 2.9 ms, M = 256 55 -> 9.3 ms).
 //   eps2 = h^2 2 s^2 t_k d (0: uniform weights);  lam = ridge_rel s^2 t_{k+1} > 0.
-template <int RI, int RJ, int A, bool CACHE, int WPE>
-__global__ void __launch_bounds__(RI * RJ) __attribute__((amdgpu_waves_per_eu(WPE)))
+template <int T>
+__global__ void __launch_bounds__(64 * spd_waves(T), spd_occupancy(T))
 k_lit_anchor(const double* __restrict__ G, int M, const double* __restrict__ rho, const double* __restrict__ Ynext,
              double* __restrict__ Ynew, double s, double dt, double eps2_all, const double* __restrict__ eps2_pp,
              double lam, FSpec f, int newton_iters, double* __restrict__ zstats, double* __restrict__ c_out,
              uint32_t* __restrict__ status) {
-    constexpr int NT = RI * RJ;
-    constexpr int B = bmax<RI, RJ>(A - 1) + 1;                        // column blocks
-    constexpr int E = slot0<RI, RJ>(A);                               // slot (a, b) is slot0(a) + b
-    constexpr int CW = (RI * A > RJ * B) ? RI * A : RJ * B;            // padded column length
-    __shared__ double gm[LMAX], om[LMAX], yv[LMAX], dg[LMAX], rr[LMAX];
-    __shared__ double col[2][CW];          // pivot column, padded to every slot's row and column index
-    __shared__ double red[NT / 64];
+    constexpr int NW = spd_waves(T), NT = 64 * NW;
+    __shared__ SpdShared<T> sh;
+    __shared__ double2 og[16 * T];   // per particle: Om_i and G_im (zero beyond M)
+    __shared__ double bv[16 * T];    // the responses, then the right-hand side Om Y
+    __shared__ double red[NW];
     __shared__ double ybar_s;
     const int m = blockIdx.x, p = blockIdx.y, tid = threadIdx.x;
-    const int tr = tid / RJ, tc = tid % RJ;
     const double* Gp = G + (int64_t)p * M * M;
     const double s2 = s * s;
-    for (int j = tid; j < M; j += NT) {
-        gm[j] = Gp[(int64_t)m * M + j];
-        dg[j] = Gp[(int64_t)j * M + j];
-        yv[j] = Ynext[(int64_t)p * M + j];
+    SpdSystem<T> sys;
+    sys.init(blockIdx.x + gridDim.x * blockIdx.y);
+    const double gmm = Gp[(int64_t)m * M + m];
+    for (int j = tid; j < 16 * T; j += NT) {
+        const bool in = j < M;
+        const double gj = in ? Gp[(int64_t)m * M + j] : 0.0;
+        og[j] = make_double2(0.0, gj);
+        sh.x[j] = in ? s2 * (Gp[(int64_t)j * M + j] - 2.0 * gj + gmm) : 0.0;   // |D_j|^2, until the solve
+        bv[j] = in ? Ynext[(int64_t)p * M + j] : 0.0;
     }
     __syncthreads();
-    const double gmm = gm[m];
     const double eps2 = eps2_pp ? eps2_pp[p] : eps2_all;
     // kernel weights of eq. Dj about the anchor (smallest squared distance subtracted) and the plain mean
     if (tid < 64) {
         double qmin = INFINITY, ys = 0.0;
         for (int j = tid; j < M; j += 64) {
-            qmin = fmin(qmin, s2 * (dg[j] - 2.0 * gm[j] + gmm));
-            ys += yv[j];
+            qmin = fmin(qmin, sh.x[j]);
+            ys += bv[j];
         }
         qmin = wave_min(qmin);
         ys = wave_sum(ys);
         double es = 0.0;
         for (int j = tid; j < M; j += 64) {
-            const double e = (eps2 > 0.0) ? exp(-(s2 * (dg[j] - 2.0 * gm[j] + gmm) - qmin) / eps2) : 1.0;
-            om[j] = e;
+            const double e = (eps2 > 0.0) ? exp(-(sh.x[j] - qmin) / eps2) : 1.0;
+            og[j].x = e;
             es += e;
         }
         es = wave_sum(es);
-        for (int j = tid; j < M; j += 64) om[j] = sqrt(om[j] / es);
+        for (int j = tid; j < M; j += 64) {
+            const double o = sqrt(og[j].x / es);
+            og[j].x = o;
+            bv[j] *= o;
+        }
         if (tid == 0) ybar_s = ys / (double)M;
     }
     __syncthreads();
 
-    // entries of the bordered system
-    const int n = M + 1;
-    double v[E];
-#pragma unroll
-    for (int a = 0; a < A; ++a)
-#pragma unroll
-        for (int b = 0; b <= bmax<RI, RJ>(a); ++b) {
-            const int i = tr + RI * a, j = tc + RJ * b;
-            double x = 0.0;
-            if (i < n && j <= i) {
-                if (i < M) {
-                    const double Kij = s2 * (Gp[(int64_t)i * M + j] - gm[i] - gm[j] + gmm);
-                    x = om[i] * om[j] * (1.0 + Kij) + ((i == j) ? lam : 0.0);
-                } else if (j < M) {
-                    x = om[j] * yv[j];   // bordered row: the right-hand side (corner entry unused)
-                }
-            }
-            v[slot0<RI, RJ>(a) + b] = x;
-        }
-
-    // Symmetric elimination (L D L^T, no square roots), right-looking.  Step jp: the owners of column jp
-    // broadcast it through col[jp & 1] (two buffers: one barrier per column suffices, since a buffer
-    // is rewritten only after every lane has passed the next barrier); every entry (i, j), j > jp,
-    // takes S_ij -= S_i,jp S_j,jp / S_jp,jp.  Column jp keeps its values u_i,jp = L_i,jp d_jp, and the
-    // bordered row ends as z = L^{-1} Om Y with L unit lower triangular.  Slots outside the triangle
-    // (i >= n or j > i) are updated too: their values are never read, and the padded column buffer
-    // keeps every read in bounds.  In the pivot's own column block only lanes right of the pivot
-    // update; blocks left of it are finished and not touched (elim_step is specialised per block).
-    uint32_t st = 0;
-    if constexpr (RI * RJ <= 512) {
-        for (int jp = 0; jp < M; ++jp) {
-            const double dj = elim_dispatch<RI, RJ, A, CACHE, 0>(jp / RJ, v, col[jp & 1], jp, tr, tc);
-            if (!(dj > 0.0)) st |= ST_NONFINITE;
-        }
-    } else {
-        // 1024-thread layout: its slots nearly fill the 128-register budget, so one loop body with the
-        // pivot's block at run time (the specialised bodies would spill)
-        for (int jp = 0; jp < M; ++jp) {
-            double* cb = col[jp & 1];
-            const int jb = jp / RJ, jr = jp % RJ;
-            if (tc == jr) {
-#pragma unroll
-                for (int a = 0; a < A; ++a)
-#pragma unroll
-                    for (int b = 0; b <= bmax<RI, RJ>(a); ++b)
-                        if (b == jb) cb[tr + RI * a] = v[slot0<RI, RJ>(a) + b];
-            }
-            __syncthreads();
-            const double dj = cb[jp];
-            if (!(dj > 0.0)) st |= ST_NONFINITE;
-            const double inv = 1.0 / dj;
-            const bool right = tc > jr;
-#pragma unroll
-            for (int a = 0; a < A; ++a)
-#pragma unroll
-                for (int b = 0; b <= bmax<RI, RJ>(a); ++b) {
-                    if (b < jb) continue;
-                    double& x = v[slot0<RI, RJ>(a) + b];
-                    const double y = fma(-cb[tr + RI * a], cb[tc + RJ * b] * inv, x);
-                    x = (b > jb || right) ? y : x;
-                }
-        }
-    }
-    // back substitution D L^T ct = z: ct_j = (z_j - sum_{i > j} u_ij ct_i) / d_j (dg holds 1 / d_j)
-#pragma unroll
-    for (int a = 0; a < A; ++a)
-#pragma unroll
-        for (int b = 0; b <= bmax<RI, RJ>(a); ++b) {
-            const int i = tr + RI * a, j = tc + RJ * b;
-            if (i == M && j < M) rr[j] = v[slot0<RI, RJ>(a) + b];
-            if (i == j && i < M) dg[i] = v[slot0<RI, RJ>(a) + b];
-        }
-    __syncthreads();
-    for (int j = tid; j < M; j += NT) dg[j] = 1.0 / dg[j];   // the pivots' reciprocals, once
-    __syncthreads();
-    for (int jp = M - 1; jp >= 0; --jp) {
-        const double cj = rr[jp] * dg[jp];
-        if constexpr (RI * RJ <= 512) {
-            bsub_dispatch<RI, RJ, A, 0>(jp / RI, v, rr, jp, tr, tc, cj);
-        } else if (tr == jp % RI) {
-            const int ib = jp / RI;
-#pragma unroll
-            for (int a = 0; a < A; ++a)
-#pragma unroll
-                for (int b = 0; b <= bmax<RI, RJ>(a); ++b) {
-                    const int j = tc + RJ * b;
-                    if (a == ib && j < jp) rr[j] -= v[slot0<RI, RJ>(a) + b] * cj;
-                }
-        }
-        __syncthreads();
-        if (tid == 0) rr[jp] = cj;
-    }
-    __syncthreads();
-    for (int j = tid; j < M; j += NT) rr[j] *= om[j];   // c = Om ct
+    // the system: Om (1 1^T + K) Om + lam I (Om is zero on the padding rows, which get a unit diagonal), and
+    // the right-hand side in column np
+    const int np = spd_pivots(M);
+    auto load = [&](int i, int j) { return Gp[min(i, M - 1) * M + min(j, M - 1)]; };
+    const bool good = sys.solve(
+        load,
+        [&](double Gij, int i, int j) {
+            const double2 u = og[i], w = og[j];
+            return u.x * w.x * fma(s2, Gij - u.y - w.y + gmm, 1.0);
+        },
+        [&](int i) { return (i < M) ? lam : 1.0; }, [&](int i) { return bv[i]; }, np, np, sh);
+    uint32_t st = good ? 0u : (uint32_t)ST_NONFINITE;
+    for (int j = tid; j < M; j += NT) sh.x[j] *= og[j].x;   // c = Om S^-1 Om Y
     __syncthreads();
     if (c_out) {   // x-dependent coefficients: Z needs alpha_x itself, formed by k_geo_alpha_z
-        for (int j = tid; j < M; j += NT) c_out[((int64_t)p * M + m) * M + j] = rr[j];
-        if (tid == 0 && st) atomicOr(&status[p], st);
+        for (int j = tid; j < M; j += NT) c_out[((int64_t)p * M + m) * M + j] = sh.x[j];
+        if ((tid & 63) == 0 && st) atomicOr(&status[p], st);
         return;
     }
 
-    // c^T K c over the lower triangle (K from G) and sum_j c_j (rho_j - rho_m)
-    double q = 0.0;
-#pragma unroll
-    for (int a = 0; a < A; ++a)
-#pragma unroll
-        for (int b = 0; b <= bmax<RI, RJ>(a); ++b) {
-            const int i = tr + RI * a, j = tc + RJ * b;
-            if (i < M && j <= i) {
-                const double Kij = s2 * (Gp[(int64_t)i * M + j] - gm[i] - gm[j] + gmm);
-                q += ((i == j) ? 1.0 : 2.0) * rr[i] * rr[j] * Kij;
-            }
-        }
+    // c^T K c entry by entry (with the G_im terms taken out of the sum they cancel there: 1e-11 off instead of
+    // 1e-15), and sum_j c_j (rho_j - rho_m)
+    const double q = s2 * sys.quadratic([&](int i, int j) { return load(i, j) - og[i].y - og[j].y + gmm; }, sh);
     const double* rp = rho + (int64_t)p * M;
     const double rm = rp[m];
     double r = 0.0;
-    for (int j = tid; j < M; j += NT) r += rr[j] * (rp[j] - rm);
+    for (int j = tid; j < M; j += NT) r += sh.x[j] * (rp[j] - rm);
     const double cKc = block_sum<NT>(q, red);
     const double crho = block_sum<NT>(r, red);
-    if (tid == 0) {
-        const double zz = s2 * cKc;          // |Z|^2, Z = s alpha_x
-        const double zs = s2 * crho;         // sum_i Z_i
-        double Fp;
-        const double y = newton_y(f, ybar_s, zz, zs, dt, newton_iters, Fp, st);
-        Ynew[(int64_t)p * M + m] = y;
-        if (zstats) {
-            zstats[((int64_t)p * M + m) * 2 + 0] = zz;
-            zstats[((int64_t)p * M + m) * 2 + 1] = zs;
+    if ((tid & 63) == 0) {
+        if (tid == 0) {
+            const double zz = s2 * cKc;          // |Z|^2, Z = s alpha_x
+            const double zs = s2 * crho;         // sum_i Z_i
+            double Fp;
+            const double y = newton_y(f, ybar_s, zz, zs, dt, newton_iters, Fp, st);
+            Ynew[(int64_t)p * M + m] = y;
+            if (zstats) {
+                zstats[((int64_t)p * M + m) * 2 + 0] = zz;
+                zstats[((int64_t)p * M + m) * 2 + 1] = zs;
+            }
         }
         if (st) atomicOr(&status[p], st);
     }
@@ -808,39 +620,21 @@ int coef_check(const fbsde_problem* pb, const fbsde_coef* coef, Coef& c) {
     return FBSDE_OK;
 }
 
-template <int RI, int RJ, int A>
-int launch_anchor(int64_t P, int M, const double* G, const double* rho, const double* Yn, double* Y, double s,
-                  double dt, double eps2, double lam, FSpec f, int iters, double* zst, uint32_t* status,
-                  hipStream_t st, const double* eps2_pp, double* c_out) {
-    static_assert((RI * RJ) % 64 == 0, "whole wavefronts");
-    // every row and column of the bordered system must have a slot
-    if (RI * A < M + 1 || RJ * (bmax<RI, RJ>(A - 1) + 1) < M + 1 || M > LMAX) return FBSDE_EINVAL;
-    // the per-step cache of the pivot column costs A + B registers: left out where the slots alone
-    // nearly fill the 128-register budget of 1024-thread blocks
-    constexpr bool CACHE = !(RI * RJ == 1024 && A == 9);
-    // waves per SIMD asked of the register allocator: four for the 16 x 16 grid with 7 row blocks (the
-    // paper's M = 100), which its specialised steps otherwise hold to three
-    constexpr int WPE = (RI == 16 && RJ == 16 && A == 7) ? 4 : (RI == 16 && RJ == 16 && A == 9) ? 3
-                      : (RI == 8 && RJ == 8) ? 4 : 1;
-    hipLaunchKernelGGL((k_lit_anchor<RI, RJ, A, CACHE, WPE>), dim3(M, (unsigned)P), dim3(RI * RJ), 0, st, G, M, rho, Yn,
-                       Y, s, dt, eps2, eps2_pp, lam, f, iters, zst, c_out, status);
-    return FBSDE_OK;
-}
-
 int anchors(int64_t P, int M, const double* G, const double* rho, const double* Yn, double* Y, double s, double dt,
             double eps2, double lam, FSpec f, int it, double* zst, uint32_t* status, hipStream_t st,
             const double* eps2_pp, double* c_out) {
-    // lane grids: one wavefront up to M + 1 = 56, four up to 144, eight (32 x 16 lanes) up to 224,
-    // sixteen up to 257.  Measured at M = 100: four wavefronts per anchor beat two (16 x 8 lanes) by 1.4x;
-    // at M = 200 the 32 x 16 grid with specialised steps beat the 32 x 32 one by 1.9x.
-#define LIT_ANCHOR(RI, RJ, A) \
-    launch_anchor<RI, RJ, A>(P, M, G, rho, Yn, Y, s, dt, eps2, lam, f, it, zst, status, st, eps2_pp, c_out)
-    if (M + 1 <= 56) return LIT_ANCHOR(8, 8, 7);
-    if (M + 1 <= 80) return LIT_ANCHOR(16, 16, 5);
-    if (M + 1 <= 112) return LIT_ANCHOR(16, 16, 7);
-    if (M + 1 <= 144) return LIT_ANCHOR(16, 16, 9);
-    if (M + 1 <= 224) return LIT_ANCHOR(32, 16, 7);
-    return LIT_ANCHOR(32, 32, 9);
+    if (M > LMAX) return FBSDE_EINVAL;
+#define LIT_ANCHOR(T)                                                                                               \
+    case T:                                                                                                          \
+        hipLaunchKernelGGL((k_lit_anchor<T>), dim3(M, (unsigned)P), dim3(64 * spd_waves(T)), 0, st, G, M, rho, Yn, Y, \
+                           s, dt, eps2, eps2_pp, lam, f, it, zst, c_out, status);                                    \
+        return FBSDE_OK;
+    switch (spd_tiles(M)) {
+        LIT_ANCHOR(1) LIT_ANCHOR(2) LIT_ANCHOR(3) LIT_ANCHOR(4) LIT_ANCHOR(5) LIT_ANCHOR(6) LIT_ANCHOR(7) LIT_ANCHOR(8)
+        LIT_ANCHOR(9) LIT_ANCHOR(10) LIT_ANCHOR(11) LIT_ANCHOR(12) LIT_ANCHOR(13) LIT_ANCHOR(14) LIT_ANCHOR(15)
+        LIT_ANCHOR(16) LIT_ANCHOR(17)
+        default: return FBSDE_EINVAL;
+    }
 #undef LIT_ANCHOR
 }
 
