@@ -134,12 +134,15 @@ typedef struct fbsde_problem {
 } fbsde_problem;
 
 /* The level's ridge solve in the per-point form (fbsde_solve and the entry points built on it):
- * FBSDE_SOLVER_AUTO takes the direct dual solve where the design is rank-deficient and small
- * (d / 8 <= M <= d + 1, M <= FBSDE_DUAL_MAXM, ridge_rel > 0, cg_fixed_iters = 0): the M x M system
- * (W^1/2 D' D'^T W^1/2 + lambda I) c = W^1/2 (Y - Ybar), alpha_x = D'^T W^1/2 c (the push-through
- * identity of the normal equations, Sec. 2.4's system in its dual form), factored by Cholesky, with
- * cg_iters_out 0 for those levels; every other level, and every level with FBSDE_SOLVER_CG, runs the
- * matrix-free CG.  The reverse mode always runs CG. */
+ * FBSDE_SOLVER_AUTO takes a direct solve where one side of the design is small (ridge_rel > 0 and
+ * cg_fixed_iters = 0 in both forms), with cg_iters_out 0 for those levels:
+ *   dual (d / 8 <= M <= d + 1, M <= FBSDE_DUAL_MAXM): the M x M system
+ *     (W^1/2 D' D'^T W^1/2 + lambda I) c = W^1/2 (Y - Ybar), alpha_x = D'^T W^1/2 c (the push-through
+ *     identity of the normal equations, Sec. 2.4's system in its dual form);
+ *   primal (M > d + 1, d <= 128, cg_maxit >= d): Sec. 2.4's d x d system itself;
+ * factored by Cholesky.  Every other level, and every level with FBSDE_SOLVER_CG, runs the matrix-free CG;
+ * so does a primal level whose workspace has no room for the d x d systems.  The reverse mode always runs
+ * CG. */
 enum { FBSDE_SOLVER_AUTO = 0, FBSDE_SOLVER_CG = 1 };
 #define FBSDE_DUAL_MAXM 128
 

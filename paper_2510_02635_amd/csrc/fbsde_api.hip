@@ -5,7 +5,6 @@
 #include "fbsde_kernels.hpp"
 #include "fbsde_adjoint.hpp"
 #include "fbsde_cgloop.hpp"
-#include "fbsde_dual.hpp"
 #include "fbsde_coef_adjoint.hpp"
 
 #include <atomic>
@@ -114,7 +113,7 @@ struct WS {
     double *x, *r, *pv, *qv, *Wbar;
     double *part1, *part2, *part3, *psc, *scal;
     int *iscal, *active;
-    double *dK, *drhs;   // the direct dual solve's M x M systems and right-hand sides (plan.dual)
+    double *dpart, *dcoef;   // the direct solve's Gram matrices and dual coefficients (plan.direct)
     int* cnt;       // CG arrival counters [P][ncnt]
     int ncnt;
     unsigned long long* queue;   // CG work queues [nq][qcap]
@@ -169,11 +168,6 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
     ws.scal = (double*)take((size_t)P * NS * 8);
     ws.iscal = (int*)take((size_t)P * 4 * 4);
     ws.active = (int*)take(64);
-    ws.dK = ws.drhs = nullptr;
-    if (pl.dual) {
-        ws.dK = (double*)take((size_t)P * pl.M * pl.M * 8);
-        ws.drhs = (double*)take((size_t)P * pl.M * 8);
-    }
     ws.tY = ws.tw = ws.tax = ws.tWbar = ws.tscal = nullptr;
     ws.tag = nullptr;
     ws.G = ws.cbar = ws.adj = nullptr;
@@ -199,7 +193,25 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
     // within a launch, so a producer never waits for a taker
     ws.qcap = (P + ws.nq - 1) / ws.nq * (int64_t)pl.nchunk * (int64_t)pl.maxit;
     ws.queue = (unsigned long long*)take((size_t)ws.nq * ws.qcap * 8);
+    ws.dpart = ws.dcoef = nullptr;
+    if (pl.direct) {
+        ws.dpart = (double*)take(direct_part_bytes(pl, P));
+        ws.dcoef = (double*)take(direct_coef_bytes(pl, P));
+    }
     return off;
+}
+
+// The plan for a workspace of `bytes`: where it does not hold the direct solve's partial Gram matrices, fewer
+// slices of them, and at last the CG in the primal form's place (it needs none; the dual form's one slice is no
+// larger than the M x M matrix).  Returns whether it fits.
+bool fit_plan(Plan& pl, int64_t P, int flags, size_t bytes) {
+    WS ws;
+    while (carve(pl, P, flags, nullptr, ws) > bytes) {
+        if (pl.direct && pl.dsplit > 1) pl.dsplit = (pl.dsplit + 1) / 2;
+        else if (pl.direct == DIRECT_PRIMAL) pl.direct = DIRECT_NONE;
+        else return false;
+    }
+    return true;
 }
 
 // -------------------------------------------------------------------- launch sequences
@@ -358,6 +370,7 @@ int run_level(const fbsde_problem* pb, const Plan& pl, int64_t P, int k, const S
     const double s2 = pb->s * pb->s;
     const double eps2 = (pb->eps_h > 0.0) ? pb->eps_h * pb->eps_h * s2 * t_next * (double)pl.d : 0.0;
     const double lam = pb->ridge_rel * s2 * t_next;
+    if (pl.direct) warm = 0;   // nothing to start from
     // x-dependent coefficients: the point's own bandwidth h^2 V_{k+1} and ridge ridge_rel V_{k+1} / d
     const double* vt = ws.coef ? ws.coefV + (k + 1) : nullptr;
     const int vstride = (int)pl.N + 1;
@@ -383,12 +396,9 @@ int run_level(const fbsde_problem* pb, const Plan& pl, int64_t P, int k, const S
                        pl.nchunk, vc, pl.ld, pb->s, lam, warm, Wbar_out, ws.x, ws.r, ws.pv, ws.scal, NS, ws.iscal,
                        ws.active, vt, vstride, pb->ridge_rel / (double)pl.d);
     int iters = 0;
-    if (pl.dual) {   // small rank-deficient cloud: the M x M dual system, factored
-        hipLaunchKernelGGL((k_dual_gram<S>), dim3((unsigned)P), dim3(256), 0, st, W, ldw, (int)pl.M, (int)pl.d, pl.ld,
-                           pb->s, Wbar_out, w_out, Y_next, ws.scal, NS, ws.dK, ws.drhs);
-        hipLaunchKernelGGL((k_dual_solve<S>), dim3((unsigned)P), dim3(256), 0, st, ws.dK, ws.drhs, (int)pl.M, W, ldw,
-                           (int)pl.d, pl.ld, pb->s, Wbar_out, w_out, ws.x, ws.iscal, status);
-        err = last_error();
+    if (pl.direct) {   // one side of the design is small: its system, factored
+        err = direct_solve<S>(pl, P, W, ldw, pb->s, Wbar_out, w_out, Y_next, ws.r, ws.scal, ws.dpart, ws.dcoef, ws.x,
+                              ws.iscal, status, st);
     } else {
         iters = r64 ? run_cg<S, double>(pb, pl, P, W, ldw, w_out, Wbar_out, ws, status, st, err)
                     : run_cg<S, S>(pb, pl, P, W, ldw, w_out, Wbar_out, ws, status, st, err);
@@ -849,7 +859,7 @@ int fbsde_solve_step(const fbsde_problem* pb, int64_t P, int32_t k, const double
     if (P == 0) return FBSDE_OK;   // nothing is read or written; the pointers may be null
     if (!W || !Y_next || !Y || Y == Y_next || !status || !wsp) return FBSDE_EINVAL;
     WS ws;
-    if (carve(pl, P, 0, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, 0, ws_bytes)) return FBSDE_ENOSPC;
     carve(pl, P, 0, (char*)wsp, ws);
     hipStream_t st = (hipStream_t)stream;
     int err = FBSDE_OK;
@@ -888,7 +898,7 @@ int fbsde_solve(const fbsde_problem* pb, int64_t P, const double* x0, double* u,
         return solve_shared(pb, P, x0, u, grad, status, wsp, ws_bytes, flags, (hipStream_t)stream);
     }
     WS ws;
-    if (carve(pl, P, flags, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, flags, ws_bytes)) return FBSDE_ENOSPC;
     carve(pl, P, flags, (char*)wsp, ws);
     const bool tape = (flags & FBSDE_WS_TAPE) != 0;
     hipStream_t st = (hipStream_t)stream;
@@ -948,7 +958,7 @@ int solve_per_point_terminal(const fbsde_problem* pb, int64_t P, const double* x
     if (P == 0) return FBSDE_OK;
     if (!x0 || !u || !status || !wsp) return FBSDE_EINVAL;
     WS ws;
-    if (carve(pl, P, flags, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, flags, ws_bytes)) return FBSDE_ENOSPC;
     carve(pl, P, flags, (char*)wsp, ws);
     ws.terminal = &terminal;
     const bool tape = (flags & FBSDE_WS_TAPE) != 0;
@@ -1142,7 +1152,7 @@ int backward_entry(const fbsde_problem* pb, int64_t P, const double* x0, const d
         return backward_shared(pb, P, x0, u_bar, x0_bar, gp_bar, fp_bar, status, wsp, ws_bytes, (hipStream_t)stream);
     }
     WS ws;
-    if (carve(pl, P, FBSDE_WS_TAPE, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, FBSDE_WS_TAPE, ws_bytes)) return FBSDE_ENOSPC;
     carve(pl, P, FBSDE_WS_TAPE, (char*)wsp, ws);
     ws.adjh = hooks;
     hipStream_t st = (hipStream_t)stream;
@@ -1180,7 +1190,7 @@ int solve_tile(const fbsde_problem* pb, int64_t P, const double* x0, double* u, 
     if ((rc = make_plan(pb, P, pl))) return rc;
     if (!x0 || !u || !status || !wsp) return FBSDE_EINVAL;
     WS ws;
-    if (carve(pl, P, flags, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, flags, ws_bytes)) return FBSDE_ENOSPC;
     carve(pl, P, flags, (char*)wsp, ws);
     const bool tape = (flags & FBSDE_WS_TAPE) != 0;
     if (pb->prec == FBSDE_F64)
@@ -1246,7 +1256,7 @@ int fbsde_time_kernel(const fbsde_problem* pb, int64_t P, int32_t which, int32_t
     if ((rc = make_plan(pb, P, pl))) return rc;
     if (!wsp || !avg_ms || reps < 1 || which < 0 || which > 4 || P == 0) return FBSDE_EINVAL;
     WS ws;
-    if (carve(pl, P, 0, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, 0, ws_bytes)) return FBSDE_ENOSPC;
     carve(pl, P, 0, (char*)wsp, ws);
     hipStream_t st = (hipStream_t)stream;
     hipEvent_t e0, e1;
@@ -1577,7 +1587,7 @@ int fbsde_solve_noalloc(const fbsde_problem* pb, int64_t P, const double* x0, do
     if (P == 0) return FBSDE_OK;
     if (!x0 || !u || !status) return FBSDE_EINVAL;
     WS ws;
-    if (carve(pl, P, 0, nullptr, ws) > (size_t)FBSDE_NOALLOC_SCRATCH_BYTES) return FBSDE_ENOSPC;
+    if (!fit_plan(pl, P, 0, (size_t)FBSDE_NOALLOC_SCRATCH_BYTES)) return FBSDE_ENOSPC;
     void* base = nullptr;
     if ((rc = scratch_of_current_device(&base))) return rc;
     carve(pl, P, 0, (char*)base, ws);

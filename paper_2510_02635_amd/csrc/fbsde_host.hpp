@@ -22,8 +22,12 @@ struct Plan {
     int ld, Q, TEAM, BS, TPW, nchunk, rows_per_chunk;
     size_t esz;
     int maxit;   // CG iterations per point and level at most (sizes the device loop's work queues)
-    bool dual;   // the forward levels use the direct dual solve (M x M Cholesky) instead of CG
+    int direct;  // the forward levels' solve: DIRECT_NONE (CG), DIRECT_DUAL (M x M), DIRECT_PRIMAL (d x d)
+    int dsplit;  // slices of the direct solve's Gram matrix
 };
+
+enum { DIRECT_NONE = 0, DIRECT_DUAL = 1, DIRECT_PRIMAL = 2 };
+constexpr int DIRECT_MAXD = 128;   // largest d of the primal direct solve
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
@@ -88,10 +92,15 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     pl.d = pb->d; pl.M = pb->M; pl.N = pb->N;
     pl.maxit = std::max(1, (int)pb->cg_maxit);
     // the direct dual solve where the cloud is small and not much thinner than d: CG iterations grow with
-    // M / d towards the near-square design (measured at M = 100: 157 per level at d = 100, 34 at d = 500,
-    // 14 at d = 1000, where the CG level is the faster one, 0.52 against 0.69 ms)
-    pl.dual = pb->solver == FBSDE_SOLVER_AUTO && !pb->shared_dw && pb->M <= FBSDE_DUAL_MAXM &&
-              pb->M <= pb->d + 1 && 8 * pb->M >= pb->d && pb->ridge_rel > 0.0 && pb->cg_fixed_iters == 0;
+    // M / d towards the near-square design (measured at M = 100: 157 per level at d = 100, 34 at d = 500)
+    pl.direct = DIRECT_NONE;
+    if (pb->solver == FBSDE_SOLVER_AUTO && !pb->shared_dw && pb->ridge_rel > 0.0 && pb->cg_fixed_iters == 0) {
+        if (pb->M <= FBSDE_DUAL_MAXM && pb->M <= pb->d + 1 && 8 * pb->M >= pb->d) pl.direct = DIRECT_DUAL;
+        // the direct primal solve where d is small: one read of the cloud instead of one per iteration
+        // (FP64, a whole solve: one point at d = 100, M = 512, N = 5 2.67 -> 0.43 ms; 512 points at d = 100,
+        // M = 1024, N = 20 80.1 -> 21.2 ms).  A cap below d asks for fewer iterations than an exact solve may take: it keeps the CG.
+        else if (pb->M > pb->d + 1 && pb->d <= DIRECT_MAXD && pb->cg_maxit >= pb->d) pl.direct = DIRECT_PRIMAL;
+    }
     pl.esz = (pb->prec == FBSDE_F64) ? 8 : 4;
     pl.ld = (int)round_up(pb->d, (pl.esz == 8) ? 16 : 32);
     const int groups = pl.ld / 4;
@@ -127,6 +136,10 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
         Plan t = pl;
         if (tn <= pl.nchunk && shape_plan(t, tt, tn)) pl = t;
     }
+    // slices of the direct solve's contraction: about 512 blocks in all, at least 32 steps each, at most 32
+    // (each costs a partial of the whole triangle)
+    const int64_t len = (pl.direct == DIRECT_PRIMAL) ? pl.M : pl.ld;
+    pl.dsplit = (int)std::max<int64_t>(1, std::min<int64_t>({512 / std::max<int64_t>(P, 1), (len + 31) / 32, 32}));
     return FBSDE_OK;
 }
 
@@ -171,6 +184,15 @@ inline bool per_point_forward_only(const fbsde_problem* pb) {
 
 inline int last_error() { return (hipGetLastError() == hipSuccess) ? FBSDE_OK : FBSDE_EHIP; }
 
+
+// The direct level solve (fbsde_direct.hip): its buffers, and the launches that leave the slope, at the scale
+// of k_moments_finish, in x.
+size_t direct_part_bytes(const Plan& pl, int64_t P);
+size_t direct_coef_bytes(const Plan& pl, int64_t P);
+template <typename S>
+int direct_solve(const Plan& pl, int64_t P, const S* W, int64_t ldw, double s, const double* Wbar, const double* w,
+                 const double* Y, const double* r, const double* scal, double* part, double* coef, double* x, int* iscal,
+                 uint32_t* status, hipStream_t st);
 
 // Entry points of the other translation units.
 size_t shared_workspace_bytes(const fbsde_problem* pb, int64_t P, int32_t flags);
