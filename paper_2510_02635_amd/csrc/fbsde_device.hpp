@@ -66,8 +66,11 @@ __device__ __forceinline__ void sincos_turn<double>(uint32_t w, double& sn, doub
     pc = pc * z + 0.5;                                 // 1/2!
     const double c_ = 1.0 - z * pc;
     const uint32_t q = ((o + 1u) >> 1) & 3u;          // angle = psi + q pi/2
-    sn = (q == 0) ? s_ : (q == 1) ? c_ : (q == 2) ? -s_ : -c_;
-    cs = (q == 0) ? c_ : (q == 1) ? -s_ : (q == 2) ? -c_ : s_;
+    // odd q swaps sin and cos, and the signs are flipped in the sign bit (sin: q = 2, 3; cos: q = 1, 2)
+    const bool sw = (q & 1u) != 0u;
+    const double a = sw ? c_ : s_, b = sw ? s_ : c_;
+    sn = __hiloint2double(__double2hiint(a) ^ (int)((q >> 1) << 31), __double2loint(a));
+    cs = __hiloint2double(__double2hiint(b) ^ (int)(((q ^ (q >> 1)) & 1u) << 31), __double2loint(b));
 }
 
 template <>

@@ -577,8 +577,9 @@ k_reverse(S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int d, int 
         team_sum2<TEAM>(lb, unused, red, team);
         bb = lb;
     }
-    // Newton runs 64 rows at a time: lane (row count mod 64) of the team's first wave keeps the row's
-    // C and |W|^2, and every 64 rows those lanes solve together instead of one lane per row
+    // Newton runs 64 rows at a time (32 on half-wave teams): lane (row count mod 64) of the team's first wave
+    // keeps the row's C and |W|^2, and every 64 rows those lanes solve together instead of one lane per row
+    constexpr int NB = G::TL < 64 ? G::TL : 64;
     int j_keep = -1;
     double c_keep = 0.0, n2_keep = 0.0, zz_keep = zz, zs_keep = zs;   // XK == 3: the particle's own Z
     auto flush = [&]() {
@@ -669,14 +670,14 @@ k_reverse(S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int d, int 
                 src = -dt * case2_source(tk, r2, Pp, Pq, (double)d, s, f.p0, f.p1, f.p2);
             }
         }
-        if (valid && L == (cnt & 63)) {
+        if (valid && L == (cnt & (NB - 1))) {
             j_keep = j;
             c_keep = alpha + s * dt_ + src;
             n2_keep = n2;
             zz_keep = zz_row;
             zs_keep = zs_row;
         }
-        if ((++cnt & 63) == 0) flush();
+        if ((++cnt & (NB - 1)) == 0) flush();
     }
     flush();
     if (st) atomicOr(&status[p], st);

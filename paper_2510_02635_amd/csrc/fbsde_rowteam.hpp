@@ -6,9 +6,11 @@
 
 namespace fbsde {
 
+// TEAM = 0: half a wavefront per row, for rows of at most 128 coordinates (32 groups of four), where a whole one
+// would leave half of its lanes idle.
 template <int Q, int TEAM>
 struct Geo {
-    static constexpr int TL = 64 * TEAM;                 // lanes per team
+    static constexpr int TL = TEAM ? 64 * TEAM : 32;     // lanes per team
     static constexpr int BS = 64 * (TEAM > 4 ? TEAM : 4);  // threads per block
     static constexpr int TPW = BS / TL;                   // teams per block
 };
@@ -71,8 +73,16 @@ __device__ __forceinline__ void store4(float* __restrict__ p, const float v[4]) 
 // For TEAM > 1 all waves of the block must call it the same number of times.
 template <int TEAM>
 __device__ __forceinline__ void team_sum2(double& a, double& b, double* red, int team) {
-    a = wave_sum(a);
-    b = wave_sum(b);
+    if constexpr (TEAM == 0) {
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) {
+            a += __shfl_xor(a, off, 64);
+            b += __shfl_xor(b, off, 64);
+        }
+    } else {
+        a = wave_sum(a);
+        b = wave_sum(b);
+    }
     if constexpr (TEAM > 1) {
         const int wv = (threadIdx.x >> 6) % TEAM, ln = threadIdx.x & 63;
         if (ln == 0) { red[2 * (team * TEAM + wv)] = a; red[2 * (team * TEAM + wv) + 1] = b; }
@@ -89,7 +99,7 @@ __device__ __forceinline__ void team_sum2(double& a, double& b, double* red, int
 // all waves of the block must call it the same number of times.
 template <int TEAM>
 __device__ __forceinline__ void team_pq(double& P, double& Q, double* red, int team) {
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int off = TEAM ? 32 : 16; off > 0; off >>= 1) {
         const double Pb = __shfl_xor(P, off, 64), Qb = __shfl_xor(Q, off, 64);
         pq_combine(P, Q, Pb, Qb);
     }
