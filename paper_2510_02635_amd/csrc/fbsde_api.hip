@@ -188,7 +188,10 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
     ws.psc = (double*)take((size_t)P * pl.nchunk * 4 * 8);
     ws.ncnt = std::max(1, cg_tree_counters(pl.nchunk));
     ws.cnt = (int*)take((size_t)P * ws.ncnt * 4);
-    ws.nq = (int)std::min<int64_t>(CG_MAXQ, std::max<int64_t>(P, 1));
+    // at most CG_MAXQ queues, and as even a share of the points in each as that allows (40 points: 20 queues of
+    // two, not 8 of two and 24 of one, whose blocks would idle for half of the time)
+    const int64_t per_queue = (std::max<int64_t>(P, 1) + CG_MAXQ - 1) / CG_MAXQ;
+    ws.nq = (int)((std::max<int64_t>(P, 1) + per_queue - 1) / per_queue);
     // a slot for every item the level can produce (its points x chunks x iterations): no slot is reused
     // within a launch, so a producer never waits for a taker
     ws.qcap = (P + ws.nq - 1) / ws.nq * (int64_t)pl.nchunk * (int64_t)pl.maxit;
@@ -202,14 +205,19 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
 }
 
 // The plan for a workspace of `bytes`: where it does not hold the direct solve's partial Gram matrices, fewer
-// slices of them, and at last the CG in the primal form's place (it needs none; the dual form's one slice is no
-// larger than the M x M matrix).  Returns whether it fits.
+// slices of them, then the CG in the primal form's place (it needs none; the dual form's one slice is no larger
+// than the M x M matrix), then fewer chunks per point (a partial vector each), down to the plan's
+// least.  Returns whether it fits.
 bool fit_plan(Plan& pl, int64_t P, int flags, size_t bytes) {
     WS ws;
     while (carve(pl, P, flags, nullptr, ws) > bytes) {
         if (pl.direct && pl.dsplit > 1) pl.dsplit = (pl.dsplit + 1) / 2;
         else if (pl.direct == DIRECT_PRIMAL) pl.direct = DIRECT_NONE;
-        else return false;
+        else if (pl.nchunk > pl.least_chunks) {
+            const int64_t n = std::max((pl.nchunk + 1) / 2, pl.least_chunks);
+            pl.rows_per_chunk = (int)((pl.M + n - 1) / n);
+            pl.nchunk = (int)((pl.M + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
+        } else return false;
     }
     return true;
 }

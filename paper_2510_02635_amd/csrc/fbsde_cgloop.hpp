@@ -13,7 +13,7 @@
 //
 // Taking items: a block holds a ticket, an index of its home queue drawn with one fetch-and-add, and the
 // item filled at that index is its next one.  Tickets may run ahead of the fill counter (the item comes
-// with a later iteration).  A block whose ticket is not filled yet takes, now and then, an item nobody
+// with a later iteration).  A block whose ticket has not been filled for a while takes an item nobody
 // holds a ticket for (an index below a queue's fill counter, claimed with a compare-and-swap of the take
 // counter), so the items of a queue whose home blocks are not resident (other kernels holding their
 // compute units) still get done, and no block ever waits on a block that is not running.  Drawing
@@ -47,6 +47,12 @@
 namespace fbsde {
 
 constexpr int CG_FAN = 8;                  // arrival-tree fan-in
+// Polls of its own ticket before a block looks for items elsewhere, about 0.1 ms.  A block that has taken someone
+// else's item is away when its own ticket fills, and nobody else may take that: its point then waits for a whole
+// chunk.  Stealing from the fourth poll on did that to every iteration whose items were not a whole number of
+// rounds over the blocks (three levels at d = 1000, M = 4096, 16 points: 24.2 -> 8.3 ms; d = 700, M = 2100, 40
+// points 43.8 -> 6.5 ms; 1024 points 176 -> 175 ms).  It is there for the queues of blocks that are not resident.
+constexpr int CG_STEAL_AFTER = 64;
 enum { ST_WAIT_LIMIT = 8 };                // status bit: a bounded device-side wait gave up
 
 // Control words of the device loop, in the workspace: the particle rows streamed by products since the
@@ -362,7 +368,7 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
             // Wave 0 finds the block's next item.  The block holds a ticket, an index of its home queue
             // taken with one fetch-and-add (no retries however many blocks share the queue): the item
             // filled at that index is the block's.  A ticket may run ahead of the fill counter (the item
-            // comes with a later iteration of a point of that queue); while it waits, the block takes
+            // comes with a later iteration of a point of that queue); where it waits long, the block takes
             // items nobody holds a ticket for (indices below a queue's fill counter, claimed with a
             // compare-and-swap of the take counter), so items of a queue whose blocks are not resident
             // still get done.  The loop is over when no point iterates any more: then no item can come
@@ -392,9 +398,9 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
                     break;
                 }
                 if (err != 0) break;
-                // every fourth round: lane q reads queue q's counters (one round trip for all queues), then
-                // the block claims an unticketed item if there is one, home queue first
-                if ((k & 3) == 3) {
+                // after CG_STEAL_AFTER rounds, every fourth: lane q reads queue q's counters (one round trip for all
+                // queues), then the block claims an unticketed item if there is one, home queue first
+                if (k >= CG_STEAL_AFTER && (k & 3) == 3) {
                     unsigned long long h = 0, tl = 0;
                     if (lane < nq) {
                         h = __hip_atomic_load(&ctl->q[lane][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

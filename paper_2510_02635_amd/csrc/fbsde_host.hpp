@@ -24,6 +24,7 @@ struct Plan {
     int maxit;   // CG iterations per point and level at most (sizes the device loop's work queues)
     int direct;  // the forward levels' solve: DIRECT_NONE (CG), DIRECT_DUAL (M x M), DIRECT_PRIMAL (d x d)
     int dsplit;  // slices of the direct solve's Gram matrix
+    int least_chunks;   // chunks per point that a smaller workspace may bring the plan down to
 };
 
 enum { DIRECT_NONE = 0, DIRECT_DUAL = 1, DIRECT_PRIMAL = 2 };
@@ -117,18 +118,31 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     if (pl.TEAM == 0) return FBSDE_EINVAL;   // d beyond 16384 (FP64) / 32768 (FP32C)
     pl.BS = 64 * std::max(pl.TEAM, 4);
     pl.TPW = pl.BS / (64 * pl.TEAM);
-    const int64_t target_blocks = 4096;
-    int64_t nchunk = (target_blocks + std::max<int64_t>(P, 1) - 1) / std::max<int64_t>(P, 1);
-    // at least 64 rows per chunk: each chunk writes one [ld] FP64 partial per pass, so the partials stay
-    // within a few per cent of the state bytes the pass reads.  Short rows (ld <= 1024) take chunks of 16
-    // rows: there a CG iteration of few points is bound by the time one chunk's rows take one after
-    // another, and summing the extra partials costs little (measured: one point at d = 100, M = 512
-    // 4.4 -> 2.7 ms per solve; 8 points at d = 1000, M = 832 20.7 -> 14.2 ms; at d >= 5000 smaller chunks
-    // were slower, the deeper arrival tree adding more than the shorter chunks save).
-    const int64_t min_rows = (pl.ld <= 1024) ? 16 : 64;
+    // Chunks per point: two work items per block that the CG loop holds on the chip at once (its registers, the
+    // bytes of a row per lane in the main, decide how many: 5, 4 or 2 blocks of 256 threads per compute unit, 1
+    // larger one).  With one item a block nothing covers the CG steps between two iterations; more items cost a
+    // partial vector and an arrival each.  At most 128 chunks a point (beyond, the arrival tree is a level
+    // deeper) unless the call has so few points that 512 items need more, at least four, and 16 rows a chunk (8
+    // on teams of eight waves and more).  Measured, three levels of a solve, before (4096 items, 64 rows above
+    // d = 1000) and now, with the loop's stealing delayed in both: d = 1000, M = 4096, 64 points 15.5 -> 13.6 ms
+    // (FP32C) and 55.1 -> 45.7 ms (FP64), 16 points 8.3 -> 4.2, 256 points 48.4 -> 46.6; d = 700, M = 2100, 40 points
+    // 6.5 -> 5.1; d = 5000, M = 600, 6 points 9.5 -> 4.4; d = 5000, M = 3712, 4 points 54.9 -> 42.3; d = 10^4, M =
+    // 1024, 16 points 15.1 -> 11.6.
+    const int row_bytes = pl.Q * 4 * (int)pl.esz;
+    const int64_t per_cu = (pl.BS > 256) ? 1 : (row_bytes <= 32) ? 5 : (row_bytes <= 64) ? 4 : 2;
+    const int64_t np = std::max<int64_t>(P, 1), min_rows = (pl.TEAM >= 8) ? 8 : 16;
+    int64_t nchunk = std::max<int64_t>({std::min<int64_t>(2 * 256 * per_cu / np, 128), 512 / np, 4});
     nchunk = std::max<int64_t>(1, std::min<int64_t>(nchunk, std::min<int64_t>(pb->M / (2 * pl.TPW), pb->M / min_rows)));
-    pl.rows_per_chunk = (int)((pb->M + nchunk - 1) / nchunk);
-    pl.nchunk = (int)((pb->M + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
+    const auto chunks = [&](int64_t n) {
+        pl.rows_per_chunk = (int)((pb->M + n - 1) / n);
+        pl.nchunk = (int)((pb->M + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
+    };
+    // 4096 items in all, 64 rows a chunk beyond ld = 1024: no more than this is asked of a workspace that is smaller
+    // than the plan's own
+    const int64_t few = std::min<int64_t>({(4096 + np - 1) / np, pb->M / (2 * pl.TPW), pb->M / ((pl.ld <= 1024) ? 16 : 64)});
+    chunks(std::max<int64_t>(1, std::min<int64_t>(nchunk, few)));
+    pl.least_chunks = pl.nchunk;
+    chunks(nchunk);
     // a shape chosen by the autotuner: never more chunks than the default, so workspaces sized
     // before the tuning still fit
     int tt, tn;
