@@ -14,16 +14,16 @@ template <typename S, int NT, bool PRIMAL>
 void gram(const Plan& pl, int64_t P, const S* W, int64_t ldw, double s, const double* Wbar, const double* w, double* part,
           int nsplit, hipStream_t st) {
     const int64_t len = PRIMAL ? pl.M : pl.ld;
-    const int slice = (int)round_up((len + nsplit - 1) / nsplit, 32);
-    hipLaunchKernelGGL((k_direct_gram<S, NT, PRIMAL>), dim3(nsplit, (unsigned)P), dim3(256), 0, st, W, ldw, (int)pl.M,
-                       pl.ld, slice, s, Wbar, w, part);
+    const int slice = (int)round_up((len + nsplit - 1) / nsplit, GRAM_SLICE);
+    hipLaunchKernelGGL((k_gram<S, NT, PRIMAL ? GRAM_PRIMAL : GRAM_DUAL>), dim3(nsplit, (unsigned)P), dim3(256), 0, st, W,
+                       ldw, (int)pl.M, pl.ld, slice, s, Wbar, w, part, nullptr);
 }
 
 }  // namespace
 
 size_t direct_part_bytes(const Plan& pl, int64_t P) {
     const int nt = (direct_n(pl) + 15) / 16;
-    return (size_t)P * pl.dsplit * direct_ntile(nt) * 256 * 8;
+    return (size_t)P * pl.dsplit * gram_ntile(nt) * 256 * 8;
 }
 size_t direct_coef_bytes(const Plan& pl, int64_t P) {
     return (pl.direct == DIRECT_DUAL) ? (size_t)P * (pl.M + 1) * 8 : 0;
@@ -45,7 +45,7 @@ int direct_solve(const Plan& pl, int64_t P, const S* W, int64_t ldw, double s, c
 #undef FB_GRAM
         default: return FBSDE_EINVAL;
     }
-    const int64_t ne = (int64_t)direct_ntile(nt) * 256;
+    const int64_t ne = (int64_t)gram_ntile(nt) * 256;
     if (nsplit > 1)
         hipLaunchKernelGGL(k_direct_fold, dim3((unsigned)(ne / 256), (unsigned)P), dim3(256), 0, st, part, nsplit, ne);
     switch (spd_tiles(n)) {

@@ -5,8 +5,8 @@
 //   primal  (M > d + 1, d <= DIRECT_MAXD): (B^T B + lambda I) alpha_x = b, one d x d system per point.
 // The matrix-free CG reads the cloud once per iteration, dozens of times a level in FP64; here it is read
 // once, for the Gram matrix on the FP64 matrix cores (FP64 arithmetic on either state).
-//   k_direct_gram   partial Gram matrices over slices of the contraction (coordinates for the dual form,
-//                   particles for the primal one), in 16 x 16 tiles of the upper triangle;
+//   k_gram          partial Gram matrices over slices of the contraction (coordinates for the dual form,
+//                   particles for the primal one), in 16 x 16 tiles of the upper triangle (fbsde_gram.hpp);
 //   k_direct_fold   the slices' partials summed in order;
 //   k_direct_solve  one block per point: factorisation and solution in registers (fbsde_spd.hpp);
 //   k_direct_alpha  dual form: alpha_x = s sum_j w_j^1/2 c_j (W_j - Wbar) over the cloud.
@@ -14,127 +14,9 @@
 // same.
 #pragma once
 #include "fbsde.h"
-#include "fbsde_rowteam.hpp"
-#include "fbsde_spd.hpp"
+#include "fbsde_gram.hpp"
 
 namespace fbsde {
-
-constexpr int direct_ntile(int nt) { return nt * (nt + 1) / 2; }
-
-__device__ __forceinline__ double2 direct_load2(const double* p) { return *reinterpret_cast<const double2*>(p); }
-__device__ __forceinline__ double2 direct_load2(const float* p) {
-    const float2 v = *reinterpret_cast<const float2*>(p);
-    return make_double2((double)v.x, (double)v.y);
-}
-
-// Partial Gram matrix of point blockIdx.y over slice blockIdx.x of the contraction, NT tiles of 16 per side.
-// Rows of B (w_j^1/2 s (W_j - Wbar)) go through LDS 32 contraction steps at a time, the next ones loaded into
-// registers meanwhile; tile t is wave t % 4's.  The LDS row lengths keep both operand reads of an MFMA free of
-// bank conflicts: dual 36 doubles (16 lanes a row apart start 8 banks apart), primal a multiple of 16 that is
-// odd in units of 16 (two of the four row groups fill the 64 banks).  Bound at P = 64, M = 100, d = 500 by the
-// latency of its few steps per block (22 us a level; 187 us with one block a point, register blocks on the vector
-// units and a Cholesky in LDS after it that took 185 us against 35 us now); at many points by the matrix cores
-// (512 points, M = 1024, d = 100: 235 us, 32 TFLOP/s).
-template <typename S, int NT, bool PRIMAL>
-__global__ void __launch_bounds__(256)
-k_direct_gram(const S* __restrict__ W, int64_t ldw, int M, int ld, int slice, double s, const double* __restrict__ Wbar,
-              const double* __restrict__ w, double* __restrict__ part) {
-    constexpr int NTILE = direct_ntile(NT), TPW = (NTILE + 3) / 4;
-    constexpr int KC = 32;
-    constexpr int STR = PRIMAL ? (NT % 2 ? 16 * NT : 16 * NT + 16) : KC + 4;
-    __shared__ double rows[PRIMAL ? KC * STR : 16 * NT * STR];
-    __shared__ double sc[PRIMAL ? KC : 16 * NT];
-    const int p = blockIdx.y, t = threadIdx.x, lane = t & 63, g = lane >> 4, c = lane & 15;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const S* Wp = W + (int64_t)p * M * ldw;
-    const double* wb = Wbar + (int64_t)p * ld;
-    const double* wp = w + (int64_t)p * M;
-    const int k0 = blockIdx.x * slice, k1 = min(k0 + slice, PRIMAL ? M : ld);
-    spd_v4 acc[TPW];
-    int to[TPW];   // LDS offsets of the tile's two operands, i | j << 16 in rows of 16
-    {
-        int i = 0, j = wave;
-#pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            while (i < NT && j >= NT) { ++i; j += i - NT; }
-            to[q] = __builtin_amdgcn_readfirstlane((i < NT) ? (i | (j << 16)) : 0);
-            j += 4;
-            acc[q] = spd_v4{0.0, 0.0, 0.0, 0.0};
-        }
-    }
-    double2 nx[NT];
-    double ns = 0.0;
-    auto fetch = [&](int kc) {
-#pragma unroll
-        for (int q = 0; q < NT; ++q) {
-            const int e = t + 256 * q;
-            double2 v = make_double2(0.0, 0.0);
-            if constexpr (PRIMAL) {
-                const int j = kc + e / (8 * NT), i = 2 * (e % (8 * NT));
-                if (j < k1) {
-                    v = direct_load2(Wp + (int64_t)j * ldw + i);
-                    v.x -= wb[i];
-                    v.y -= wb[i + 1];
-                }
-            } else {
-                const int r = e >> 4, i = kc + 2 * (e & 15);
-                if (r < M && i < k1) {
-                    v = direct_load2(Wp + (int64_t)r * ldw + i);
-                    v.x -= wb[i];
-                    v.y -= wb[i + 1];
-                }
-            }
-            nx[q] = v;
-        }
-        if constexpr (PRIMAL) {
-            if (t < KC) ns = (kc + t < k1) ? s * sqrt(wp[kc + t]) : 0.0;
-        }
-    };
-    if constexpr (!PRIMAL) {
-        for (int r = t; r < 16 * NT; r += 256) sc[r] = (r < M) ? s * sqrt(wp[r]) : 0.0;
-    }
-    if (k0 < k1) fetch(k0);
-    for (int kc = k0; kc < k1; kc += KC) {
-        __syncthreads();   // the rows of the step before have been read
-        if constexpr (PRIMAL) {
-            if (t < KC) sc[t] = ns;
-            __syncthreads();
-        }
-#pragma unroll
-        for (int q = 0; q < NT; ++q) {
-            const int e = t + 256 * q;
-            const int r = PRIMAL ? e / (8 * NT) : e >> 4, i = PRIMAL ? 2 * (e % (8 * NT)) : 2 * (e & 15);
-            const double f = sc[r];
-            *reinterpret_cast<double2*>(&rows[r * STR + i]) = make_double2(f * nx[q].x, f * nx[q].y);
-        }
-        __syncthreads();
-        if (kc + KC < k1) fetch(kc + KC);
-#pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            const int i = to[q] & 0xFFFF, j = to[q] >> 16;
-#pragma unroll
-            for (int h = 0; h < KC / 8; ++h) {
-                double2 a, b;
-                if constexpr (PRIMAL) {
-                    a = make_double2(rows[(8 * h + g) * STR + 16 * i + c], rows[(8 * h + 4 + g) * STR + 16 * i + c]);
-                    b = make_double2(rows[(8 * h + g) * STR + 16 * j + c], rows[(8 * h + 4 + g) * STR + 16 * j + c]);
-                } else {   // the order of the contraction is the same permutation for both operands
-                    a = *reinterpret_cast<const double2*>(&rows[(16 * i + c) * STR + 8 * h + 2 * g]);
-                    b = *reinterpret_cast<const double2*>(&rows[(16 * j + c) * STR + 8 * h + 2 * g]);
-                }
-                acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, acc[q], 0, 0, 0);
-                acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, acc[q], 0, 0, 0);
-            }
-        }
-    }
-    double* out = part + ((int64_t)p * gridDim.x + blockIdx.x) * NTILE * 256;
-#pragma unroll
-    for (int q = 0; q < TPW; ++q)
-        if (wave + 4 * q < NTILE) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) out[(wave + 4 * q) * 256 + 64 * r + lane] = acc[q][r];
-        }
-}
 
 // part[p][0][.] = sum over the slices, in order; grid (elements / 256, P).
 __global__ void __launch_bounds__(256)

@@ -150,10 +150,15 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
         Plan t = pl;
         if (tn <= pl.nchunk && shape_plan(t, tt, tn)) pl = t;
     }
-    // slices of the direct solve's contraction: about 512 blocks in all, at least 32 steps each, at most 32
-    // (each costs a partial of the whole triangle)
+    // slices of the direct solve's contraction: about two blocks a compute unit in all (as many as are resident),
+    // at least 32 indices each, at most 32 (each costs a partial of the whole triangle); with more points than
+    // units, up to four slices where that leaves the units idle for less of the last round
     const int64_t len = (pl.direct == DIRECT_PRIMAL) ? pl.M : pl.ld;
-    pl.dsplit = (int)std::max<int64_t>(1, std::min<int64_t>({512 / std::max<int64_t>(P, 1), (len + 31) / 32, 32}));
+    int64_t split = std::max<int64_t>(1, 512 / np);
+    if (np > 256)
+        for (int64_t n = 2; n <= 4; ++n)
+            if (10 * ((np * n + 255) / 256) * split < 9 * ((np * split + 255) / 256) * n) split = n;
+    pl.dsplit = (int)std::max<int64_t>(1, std::min<int64_t>({split, (len + 31) / 32, 32}));
     return FBSDE_OK;
 }
 

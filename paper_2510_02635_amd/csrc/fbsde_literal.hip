@@ -27,6 +27,7 @@
 #include <cmath>
 
 #include "fbsde_host.hpp"
+#include "fbsde_gram.hpp"
 #include "fbsde_spd.hpp"
 
 namespace {
@@ -182,87 +183,21 @@ k_lit_gram(const double* __restrict__ W, int64_t ldw, int M, int ld, int ntiles,
         }
 }
 
-// G = W W^T per point for M <= 128: one workgroup per (coordinate chunk, point) holds the chunk of all M
-// rows in LDS, 16 coordinates at a time, so each element of W is read once.  Thread t owns the BSZ x BSZ
-// output block t = bi (bi + 1) / 2 + bj (bj <= bi) of the lower block triangle; BSZ is chosen per M so
-// that there are at most 256 blocks.  The row sums rho are fused in.  Grid (nsplit, P); chunk ks writes
-// its partial matrix to Gpart[ks][P][M][M] and its row sums to Rpart[ks][P][M].
-template <int BSZ>
-__global__ void __launch_bounds__(256)
-k_lit_gram_rows(const double* __restrict__ W, int64_t ldw, int M, int ld, int chunk, double* __restrict__ Gpart,
-                double* __restrict__ Rpart) {
-    __shared__ double Ws[136][17];
-    const int ks = blockIdx.x, p = blockIdx.y, tid = threadIdx.x;
-    const int nbk = (M + BSZ - 1) / BSZ;
-    const int nblk = nbk * (nbk + 1) / 2;
-    const bool mine = tid < nblk;
-    int bi = 0;
-    if (mine) {
-        bi = (int)((sqrt(8.0 * (double)tid + 1.0) - 1.0) * 0.5);
-        while (bi * (bi + 1) / 2 > tid) --bi;
-        while ((bi + 1) * (bi + 2) / 2 <= tid) ++bi;
-    }
-    const int bj = mine ? tid - bi * (bi + 1) / 2 : 0;
-    double acc[BSZ][BSZ];
-#pragma unroll
-    for (int x = 0; x < BSZ; ++x)
-#pragma unroll
-        for (int y = 0; y < BSZ; ++y) acc[x][y] = 0.0;
-    const double* Wp = W + (int64_t)p * M * ldw;
-    const int kb = ks * chunk, ke = min(ld, kb + chunk);
-    const int rows = BSZ * nbk;
-    double rsum = 0.0;   // thread tid < M: its row's sum over the chunk
-    for (int k0 = kb; k0 < ke; k0 += 16) {
-        for (int e = tid; e < rows * 16; e += 256) {
-            const int row = e / 16, kk = e % 16;
-            Ws[row][kk] = (row < M) ? Wp[(int64_t)row * ldw + k0 + kk] : 0.0;
-        }
-        __syncthreads();
-        if (tid < M) {
-#pragma unroll
-            for (int kk = 0; kk < 16; ++kk) rsum += Ws[tid][kk];
-        }
-        if (mine) {
-#pragma unroll 4
-            for (int kk = 0; kk < 16; ++kk) {
-                double a[BSZ], b[BSZ];
-#pragma unroll
-                for (int x = 0; x < BSZ; ++x) {
-                    a[x] = Ws[BSZ * bi + x][kk];
-                    b[x] = Ws[BSZ * bj + x][kk];
-                }
-#pragma unroll
-                for (int x = 0; x < BSZ; ++x)
-#pragma unroll
-                    for (int y = 0; y < BSZ; ++y) acc[x][y] += a[x] * b[y];
-            }
-        }
-        __syncthreads();
-    }
-    if (tid < M) Rpart[((int64_t)ks * gridDim.y + p) * M + tid] = rsum;
-    double* Gp = Gpart + ((int64_t)ks * gridDim.y + p) * M * M;
-    if (mine) {
-#pragma unroll
-        for (int x = 0; x < BSZ; ++x)
-#pragma unroll
-            for (int y = 0; y < BSZ; ++y) {
-                const int i = BSZ * bi + x, j = BSZ * bj + y;
-                if (i < M && j < M) {
-                    Gp[(int64_t)i * M + j] = acc[x][y];
-                    Gp[(int64_t)j * M + i] = acc[x][y];
-                }
-            }
-    }
-}
-
 // G = sum_ks Gpart[ks] over P M M elements and, with Rpart, rho = sum_ks Rpart[ks] over nr = P M
-// elements, in chunk order (deterministic).
+// elements, in chunk order (deterministic).  upper: Gpart holds the 16 x 16 tiles of the upper triangle only, which
+// are mirrored (grid of whole matrices: element e = (p M + i) M + j).
 __global__ void __launch_bounds__(256)
-k_lit_gram_sum(const double* __restrict__ Gpart, const double* __restrict__ Rpart, int nsplit, int64_t n,
-               int64_t nr, double* __restrict__ G, double* __restrict__ rho) {
+k_lit_gram_sum(const double* __restrict__ Gpart, const double* __restrict__ Rpart, int nsplit, int M, int upper,
+               int64_t n, int64_t nr, double* __restrict__ G, double* __restrict__ rho) {
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        int64_t src = e;
+        if (upper) {
+            const int64_t row = e / M, p = row / M;
+            const int i = (int)(row - p * M), j = (int)(e - row * M);
+            if (i / 16 > j / 16) src = (p * M + j) * M + i;
+        }
         double v = 0.0;
-        for (int ks = 0; ks < nsplit; ++ks) v += Gpart[(int64_t)ks * n + e];
+        for (int ks = 0; ks < nsplit; ++ks) v += Gpart[(int64_t)ks * n + src];
         G[e] = v;
         if (Rpart && e < nr) {
             double r = 0.0;
@@ -555,9 +490,9 @@ struct Coef {
     double mu0, s0, mu1, s1;
 };
 
-// Split of the Gram contraction.  M <= 128: the row-resident kernel, one tile per point, about 1024
-// workgroups per launch; otherwise 64 x 64 tiles of the lower triangle, about 2048 workgroups.  At least
-// 256 coordinates per workgroup either way.
+// Split of the Gram contraction.  M <= 128: k_gram, the whole triangle in one block, which a compute unit holds one
+// of: about two a unit; otherwise 64 x 64 tiles of the lower triangle, about 2048 workgroups.  At least 256
+// coordinates per workgroup either way.
 struct GramSplit {
     bool rows;
     int ntiles, nsplit, chunk;
@@ -568,9 +503,9 @@ GramSplit gram_split(int64_t P, int64_t M, int64_t ld) {
     const int nb = (int)((M + 63) / 64);
     g.ntiles = g.rows ? 1 : nb * (nb + 1) / 2;
     const int64_t tp = g.ntiles * std::max<int64_t>(P, 1);   // P = 0: a size query with nothing to split
-    const int64_t want = ((g.rows ? 1024 : 2048) + tp - 1) / tp;
+    const int64_t want = ((g.rows ? 512 : 2048) + tp - 1) / tp;
     g.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(want, ld / 256));
-    g.chunk = (int)host::round_up((ld + g.nsplit - 1) / g.nsplit, 16);
+    g.chunk = (int)host::round_up((ld + g.nsplit - 1) / g.nsplit, g.rows ? GRAM_SLICE : 16);
     return g;
 }
 
@@ -639,6 +574,18 @@ int anchors(int64_t P, int M, const double* G, const double* rho, const double* 
 }
 
 // The whole literal solve for either coefficient family (arguments validated by the callers).
+void gram_rows(int64_t P, int M, const double* X, int ld, const GramSplit& gs, const LitWS& w, hipStream_t st) {
+    switch ((M + 15) / 16) {
+#define LIT_GRAM(NT)                                                                                                   \
+    case NT:                                                                                                           \
+        hipLaunchKernelGGL((k_gram<double, NT, GRAM_PLAIN>), dim3(gs.nsplit, (unsigned)P), dim3(256), 0, st, X,        \
+                           (int64_t)ld, M, ld, gs.chunk, 1.0, nullptr, nullptr, w.Gpart, w.Rpart);                     \
+        break;
+        LIT_GRAM(1) LIT_GRAM(2) LIT_GRAM(3) LIT_GRAM(4) LIT_GRAM(5) LIT_GRAM(6) LIT_GRAM(7) LIT_GRAM(8)
+#undef LIT_GRAM
+    }
+}
+
 int lit_run(const fbsde_problem* pb, const Coef& cf, const host::Plan& pl, int64_t P, int32_t k_stop,
             const double* x0, double* u, double* Y_out, double* z_stats, uint32_t* status, const LitWS& w,
             hipStream_t st, bool stored = false) {
@@ -686,22 +633,13 @@ int lit_run(const fbsde_problem* pb, const Coef& cf, const host::Plan& pl, int64
             hipLaunchKernelGGL(k_lit_reverse, dim3(rblocks), dim3(256), 0, st, w.W, (int64_t)pl.ld, M, d, k, sqdt,
                                pb->point_base, ky.k0, ky.k1, P, k == 0 ? 1 : 0);
         const long tg = host::timer_begin(st, gram_flops, FBSDE_TIMED_LITERAL_GRAM);
-        // row-resident Gram: block size per M so that at most 256 blocks cover the lower triangle
-        if (gs.rows && M <= 88)
-            hipLaunchKernelGGL(k_lit_gram_rows<4>, dim3(gs.nsplit, (unsigned)P), dim3(256), 0, st, Xk, (int64_t)pl.ld,
-                               M, pl.ld, gs.chunk, w.Gpart, w.Rpart);
-        else if (gs.rows && M <= 110)
-            hipLaunchKernelGGL(k_lit_gram_rows<5>, dim3(gs.nsplit, (unsigned)P), dim3(256), 0, st, Xk, (int64_t)pl.ld,
-                               M, pl.ld, gs.chunk, w.Gpart, w.Rpart);
-        else if (gs.rows)
-            hipLaunchKernelGGL(k_lit_gram_rows<6>, dim3(gs.nsplit, (unsigned)P), dim3(256), 0, st, Xk, (int64_t)pl.ld,
-                               M, pl.ld, gs.chunk, w.Gpart, w.Rpart);
+        if (gs.rows) gram_rows(P, M, Xk, pl.ld, gs, w, st);
         else
             hipLaunchKernelGGL(k_lit_gram, dim3(gs.ntiles * gs.nsplit, (unsigned)P), dim3(256), 0, st, Xk,
                                (int64_t)pl.ld, M, pl.ld, gs.ntiles, gs.chunk, w.Gpart);
         if (gs.nsplit > 1)
             hipLaunchKernelGGL(k_lit_gram_sum, dim3(sblocks), dim3(256), 0, st, w.Gpart, gs.rows ? w.Rpart : nullptr,
-                               gs.nsplit, nG, P * (int64_t)M, w.G, w.rho);
+                               gs.nsplit, M, gs.rows ? 1 : 0, nG, P * (int64_t)M, w.G, w.rho);
         host::timer_end(tg, st);
         if (!gs.rows && !cf.geo)
             hipLaunchKernelGGL(k_lit_rowsum, dim3(M, (unsigned)P), dim3(64), 0, st, Xk, (int64_t)pl.ld, M, pl.ld,
