@@ -409,20 +409,24 @@ int run_level(const fbsde_problem* pb, const Plan& pl, int64_t P, int k, const S
     // the CG product, whose FP32 rounding would otherwise reach the ridge-only null space of the design
     // (where the solution carries it with weight 1/lam)
     const bool r64 = !std::is_same<S, double>::value && pl.M <= pl.d + 1;
+    // the warm start's direction goes from level to level in qv, which only the CG uses in between, and the scaled
+    // slope before it in part2, which only the moments use
+    const bool ext = !pl.direct && pl.M >= 2 * pl.d;
+    const double* xw = ext ? ws.qv : ws.x;
     dispatch_rows<S>(pl, [&](auto qc, auto tc) {
         constexpr int QQ = decltype(qc)::value, TT = decltype(tc)::value;
         if (r64)
             hipLaunchKernelGGL((k_moments<S, double, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS), 0,
-                               st, W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w_out, ws.c2, ws.x, ws.scal,
+                               st, W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w_out, ws.c2, xw, ws.scal,
                                NS, warm, ws.part1, ws.part2, ws.part3, ws.psc);
         else
             hipLaunchKernelGGL((k_moments<S, S, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS), 0, st,
-                               W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w_out, ws.c2, ws.x, ws.scal, NS,
+                               W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w_out, ws.c2, xw, ws.scal, NS,
                                warm, ws.part1, ws.part2, ws.part3, ws.psc);
     });
     const int vc = fold_parts(pl, P, ws.part1, ws.part2, warm ? ws.part3 : nullptr, st);
     hipLaunchKernelGGL(k_moments_finish, dim3((unsigned)P), dim3(256), 0, st, ws.part1, ws.part2, ws.part3, ws.psc,
-                       pl.nchunk, vc, pl.ld, pb->s, lam, warm, Wbar_out, ws.x, ws.r, ws.pv, ws.scal, NS, ws.iscal,
+                       pl.nchunk, vc, pl.ld, pb->s, lam, warm, Wbar_out, ws.x, xw, ext ? 1 : 0, ws.r, ws.pv, ws.scal, NS, ws.iscal,
                        ws.active, vt, vstride, pb->ridge_rel / (double)pl.d);
     int iters = 0;
     if (pl.direct) {   // one side of the design is small: its system, factored
@@ -434,7 +438,8 @@ int run_level(const fbsde_problem* pb, const Plan& pl, int64_t P, int k, const S
     }
     if (err) return iters;
     hipLaunchKernelGGL(k_level_finish, dim3((unsigned)P), dim3(256), 0, st, ws.x, Wbar_out, pl.ld, (int)pl.d, pb->s,
-                       ws.scal, NS, alpha_out, alpha_x_out);
+                       ws.scal, NS, alpha_out, alpha_x_out, ext ? ws.qv : nullptr, (ext && warm) ? ws.part2 : nullptr,
+                       (int64_t)pl.nchunk * pl.ld);
     err = last_error();
     return iters;
 }
