@@ -19,7 +19,7 @@
 // The registers keep the raw rows, which with the steps' R^-T is all that the back substitution needs
 // (x_t = R^-1 R^-T (right-hand side - rows . x)); it goes by blocks of 16 rows.
 //
-// What bounds it is the chain of the steps: the 4 x 4 factor (two dependent reciprocal square roots), two LDS
+// What bounds it is the chain of the steps: the 4 x 4 factor (four dependent reciprocal square roots), two LDS
 // round trips and the MFMA latency, over a quarter of the columns.  So the pivot block is taken ahead by a wave
 // with little else to do, and about nine tiles a wave leave room for four waves per SIMD.
 #pragma once
@@ -134,18 +134,15 @@ struct SpdSystem {
                      p13 = spd_readlane(u, 16 + 4 * B + 3);
         const double p22 = spd_readlane(u, 32 + 4 * B + 2), p23 = spd_readlane(u, 32 + 4 * B + 3);
         const double p33 = spd_readlane(u, 48 + 4 * B + 3);
-        // 2 x 2 blocks: a block's second pivot is its determinant over the first, so that the two reciprocal
-        // square roots of a block do not wait for each other
-        const double i0 = spd_rsqrt(p00), det0 = fma(-p01, p01, p00 * p11);
-        const double i1 = spd_rsqrt(det0) * (p00 * i0);
+        // one pivot after the other: a product of pivots (a 2 x 2 determinant for two at a time) leaves the range of
+        // FP64 for matrices beyond 1e+-154, which sigma beyond 1e+-77 gives
+        const double i0 = spd_rsqrt(p00);
         const double r01 = p01 * i0, r02 = p02 * i0, r03 = p03 * i0;
+        const double q11 = fma(-r01, r01, p11), i1 = spd_rsqrt(q11);
         const double r12 = fma(-r01, r02, p12) * i1, r13 = fma(-r01, r03, p13) * i1;
-        const double q22 = fma(-r12, r12, fma(-r02, r02, p22));
-        const double q23 = fma(-r12, r13, fma(-r02, r03, p23));
-        const double q33 = fma(-r13, r13, fma(-r03, r03, p33));
-        const double det1 = fma(-q23, q23, q22 * q33);
-        const double i2 = spd_rsqrt(q22), i3 = spd_rsqrt(det1) * (q22 * i2);
-        const double r23 = q23 * i2;
+        const double q22 = fma(-r12, r12, fma(-r02, r02, p22)), i2 = spd_rsqrt(q22);
+        const double r23 = fma(-r12, r13, fma(-r02, r03, p23)) * i2;
+        const double q33 = fma(-r23, r23, fma(-r13, r13, fma(-r03, r03, p33))), i3 = spd_rsqrt(q33);
         const double m10 = -r01 * i0 * i1;
         const double m20 = -fma(r02, i0, r12 * m10) * i2, m21 = -r12 * i1 * i2;
         const double m30 = -fma(r03, i0, fma(r13, m10, r23 * m20)) * i3, m31 = -fma(r13, i1, r23 * m21) * i3,
@@ -156,7 +153,7 @@ struct SpdSystem {
             Rt[8] = m20;  Rt[9] = m21;  Rt[10] = i2;
             Rt[12] = m30; Rt[13] = m31; Rt[14] = m32;  Rt[15] = i3;
         }
-        return p00 > 0.0 && det0 > 0.0 && q22 > 0.0 && det1 > 0.0;
+        return p00 > 0.0 && q11 > 0.0 && q22 > 0.0 && q33 > 0.0;
     }
 
     // Step 2: every wave scales its share of the published rows, between two barriers.
