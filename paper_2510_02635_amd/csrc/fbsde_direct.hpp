@@ -49,23 +49,34 @@ k_direct_solve(const double* __restrict__ part, int64_t pstride, int n, int NT, 
     const double lam = scal[(int64_t)p * ns + 3];
     SpdSystem<T> sys;
     sys.init(blockIdx.x);
+    bool any = false;
     if constexpr (PRIMAL) {
-        for (int i = t; i < 16 * T; i += BS) bv[i] = (i < n) ? r[(int64_t)p * ld + i] : 0.0;
+        for (int i = t; i < 16 * T; i += BS) {
+            bv[i] = (i < n) ? r[(int64_t)p * ld + i] : 0.0;
+            any |= bv[i] != 0.0;
+        }
     } else {
         const double yb = scal[(int64_t)p * ns + 4], isc = scal[(int64_t)p * ns + 9];
-        for (int i = t; i < 16 * T; i += BS)
+        for (int i = t; i < 16 * T; i += BS) {
             bv[i] = (i < n) ? sqrt(w[(int64_t)p * n + i]) * (Y[(int64_t)p * n + i] - yb) / isc : 0.0;
+            any |= bv[i] != 0.0;
+        }
     }
-    __syncthreads();
-    const int np = spd_pivots(n);
-    const bool good = sys.solve(
-        [&](int i, int j) {
-            const int ti = i >> 4, tj = j >> 4;
-            if (tj >= NT) return 0.0;
-            return A[(ti * NT - ti * (ti - 1) / 2 + tj - ti) * 256 + (i >> 2 & 3) * 64 + (i & 3) * 16 + (j & 15)];
-        },
-        [&](double a, int, int) { return a; }, [&](int i) { return (i < n) ? lam : 1.0; },
-        [&](int i) { return bv[i]; }, np, np, sh);
+    bool good = true;
+    if (__syncthreads_or(any)) {
+        const int np = spd_pivots(n);
+        good = sys.solve(
+            [&](int i, int j) {
+                const int ti = i >> 4, tj = j >> 4;
+                if (tj >= NT) return 0.0;
+                return A[(ti * NT - ti * (ti - 1) / 2 + tj - ti) * 256 + (i >> 2 & 3) * 64 + (i & 3) * 16 + (j & 15)];
+            },
+            [&](double a, int, int) { return a; }, [&](int i) { return (i < n) ? lam : 1.0; },
+            [&](int i) { return bv[i]; }, np, np, sh);
+    } else {   // as the CG: no step from zero, also where the cloud has no spread and the system is zero
+        for (int i = t; i < 16 * T; i += BS) sh.x[i] = 0.0;
+        __syncthreads();
+    }
     if (!good && sys.lane == 0) atomicOr(&status[p], (uint32_t)ST_NONFINITE);
     if constexpr (PRIMAL) {
         for (int i = t; i < ld; i += BS) x[(int64_t)p * ld + i] = (i < n) ? sh.x[i] : 0.0;
