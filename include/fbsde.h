@@ -139,7 +139,7 @@ typedef struct fbsde_problem {
  *   dual (d / 8 <= M <= d + 1, M <= FBSDE_DUAL_MAXM): the M x M system
  *     (W^1/2 D' D'^T W^1/2 + lambda I) c = W^1/2 (Y - Ybar), alpha_x = D'^T W^1/2 c (the push-through
  *     identity of the normal equations, Sec. 2.4's system in its dual form);
- *   primal (M > d + 1, d <= 128, cg_maxit >= d): Sec. 2.4's d x d system itself;
+ *   primal (M > d + 1, d <= 128, cg_maxit >= d, ridge_rel >= 1e-8): Sec. 2.4's d x d system itself;
  * factored by Cholesky.  Every other level, and every level with FBSDE_SOLVER_CG, runs the matrix-free CG;
  * so does a primal level whose workspace has no room for the d x d systems.  The reverse mode always runs
  * CG. */

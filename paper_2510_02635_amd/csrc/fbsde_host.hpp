@@ -29,6 +29,13 @@ struct Plan {
 
 enum { DIRECT_NONE = 0, DIRECT_DUAL = 1, DIRECT_PRIMAL = 2 };
 constexpr int DIRECT_MAXD = 128;   // largest d of the primal direct solve
+// Smallest ridge of the primal direct solve.  A narrow kernel's weights leave the design with fewer particles than
+// coordinates, and what keeps the d x d matrix positive is the ridge alone: a pivot is positive for certain while the
+// ridge over the largest diagonal entry is above d (d + 1) 2^-53 (1.8e-12 at d = 128), and that entry reaches some 20
+// times the ridge's own scale s^2 t, d times it under x-dependent coefficients.  Below, the CG, which needs no
+// positive pivot (seen at kernel factors of 0.03 to 0.1: no point fails at 1e-12 and above, up to 15 of 300 at 1e-15,
+// half of them at 1e-18; from 1e-8 up the direct solve's error is at or below the CG's at every one tried).
+constexpr double DIRECT_MIN_RIDGE = 1e-8;
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
@@ -98,9 +105,11 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     if (pb->solver == FBSDE_SOLVER_AUTO && !pb->shared_dw && pb->ridge_rel > 0.0 && pb->cg_fixed_iters == 0) {
         if (pb->M <= FBSDE_DUAL_MAXM && pb->M <= pb->d + 1 && 8 * pb->M >= pb->d) pl.direct = DIRECT_DUAL;
         // the direct primal solve where d is small: one read of the cloud instead of one per iteration
-        // (FP64, a whole solve: one point at d = 100, M = 512, N = 5 2.67 -> 0.43 ms; 512 points at d = 100,
-        // M = 1024, N = 20 80.1 -> 21.2 ms).  A cap below d asks for fewer iterations than an exact solve may take: it keeps the CG.
-        else if (pb->M > pb->d + 1 && pb->d <= DIRECT_MAXD && pb->cg_maxit >= pb->d) pl.direct = DIRECT_PRIMAL;
+        // (FP64, a whole solve: one point at d = 100, M = 512, N = 5 2.67 -> 0.39 ms; 512 points at d = 100,
+        // M = 1024, N = 20 80.1 -> 12.7 ms).  A cap below d asks for fewer iterations than an exact solve may take: it
+        // keeps the CG.
+        else if (pb->M > pb->d + 1 && pb->d <= DIRECT_MAXD && pb->cg_maxit >= pb->d && pb->ridge_rel >= DIRECT_MIN_RIDGE)
+            pl.direct = DIRECT_PRIMAL;
     }
     pl.esz = (pb->prec == FBSDE_F64) ? 8 : 4;
     pl.ld = (int)round_up(pb->d, (pl.esz == 8) ? 16 : 32);
