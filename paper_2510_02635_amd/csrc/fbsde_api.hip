@@ -182,6 +182,9 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
         ws.cbar = (double*)take(PM * 8);
         ws.adj = (double*)take((size_t)P * 16 * 8);
     }
+    // From here on: the CG's buffers, which a direct solve does not use between the end of the moments and its own,
+    // so its Gram matrices lie over them.
+    const size_t cg_at = off;
     ws.part1 = (double*)take(parts * 8);
     ws.part2 = (double*)take(parts * 8);
     ws.part3 = (double*)take(parts * 8);
@@ -198,28 +201,36 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
     ws.queue = (unsigned long long*)take((size_t)ws.nq * ws.qcap * 8);
     ws.dpart = ws.dcoef = nullptr;
     if (pl.direct) {
+        const size_t cg_end = off;
+        off = cg_at;
         ws.dpart = (double*)take(direct_part_bytes(pl, P));
         ws.dcoef = (double*)take(direct_coef_bytes(pl, P));
+        off = std::max(off, cg_end);
     }
     return off;
 }
 
-// The plan for a workspace of `bytes`: where it does not hold the direct solve's partial Gram matrices, fewer
-// slices of them, then the CG in the primal form's place (it needs none; the dual form's one slice is no larger
-// than the M x M matrix), then fewer chunks per point (a partial vector each), down to the plan's
-// least.  Returns whether it fits.
+// The plan for a workspace of `bytes`.  Where the direct solve's partial Gram matrices are what does not fit: fewer
+// slices of them, then the CG in the primal form's place (it needs none; a dual form's one slice and its coefficients
+// take at most M (M + 1) + 1 doubles a point).  Otherwise fewer chunks per point (a partial vector each), down to the
+// plan's least.  Returns whether it fits.
 bool fit_plan(Plan& pl, int64_t P, int flags, size_t bytes) {
     WS ws;
-    while (carve(pl, P, flags, nullptr, ws) > bytes) {
-        if (pl.direct && pl.dsplit > 1) pl.dsplit = (pl.dsplit + 1) / 2;
-        else if (pl.direct == DIRECT_PRIMAL) pl.direct = DIRECT_NONE;
-        else if (pl.nchunk > pl.least_chunks) {
+    for (;;) {
+        const size_t need = carve(pl, P, flags, nullptr, ws);
+        if (need <= bytes) return true;
+        Plan cg = pl;
+        cg.direct = DIRECT_NONE;
+        if (need > carve(cg, P, flags, nullptr, ws)) {
+            if (pl.dsplit > 1) pl.dsplit = (pl.dsplit + 1) / 2;
+            else if (pl.direct == DIRECT_PRIMAL) pl.direct = DIRECT_NONE;
+            else return false;
+        } else if (pl.nchunk > pl.least_chunks) {
             const int64_t n = std::max((pl.nchunk + 1) / 2, pl.least_chunks);
             pl.rows_per_chunk = (int)((pl.M + n - 1) / n);
             pl.nchunk = (int)((pl.M + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
         } else return false;
     }
-    return true;
 }
 
 // -------------------------------------------------------------------- launch sequences

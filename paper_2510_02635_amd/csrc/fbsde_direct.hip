@@ -16,14 +16,13 @@ void gram(const Plan& pl, int64_t P, const S* W, int64_t ldw, double s, const do
     const int64_t len = PRIMAL ? pl.M : pl.ld;
     const int slice = (int)round_up((len + nsplit - 1) / nsplit, GRAM_SLICE);
     hipLaunchKernelGGL((k_gram<S, NT, PRIMAL ? GRAM_PRIMAL : GRAM_DUAL>), dim3(nsplit, (unsigned)P), dim3(256), 0, st, W,
-                       ldw, (int)pl.M, pl.ld, slice, s, Wbar, w, part, nullptr);
+                       ldw, (int)pl.M, pl.ld, direct_n(pl), slice, s, Wbar, w, part, nullptr);
 }
 
 }  // namespace
 
 size_t direct_part_bytes(const Plan& pl, int64_t P) {
-    const int nt = (direct_n(pl) + 15) / 16;
-    return (size_t)P * pl.dsplit * gram_ntile(nt) * 256 * 8;
+    return (size_t)P * pl.dsplit * gram_entries(direct_n(pl)) * 8;
 }
 size_t direct_coef_bytes(const Plan& pl, int64_t P) {
     return (pl.direct == DIRECT_DUAL) ? (size_t)P * (pl.M + 1) * 8 : 0;
@@ -45,18 +44,18 @@ int direct_solve(const Plan& pl, int64_t P, const S* W, int64_t ldw, double s, c
 #undef FB_GRAM
         default: return FBSDE_EINVAL;
     }
-    const int64_t ne = (int64_t)gram_ntile(nt) * 256;
+    const int64_t ne = gram_entries(n);
     if (nsplit > 1)
-        hipLaunchKernelGGL(k_direct_fold, dim3((unsigned)(ne / 256), (unsigned)P), dim3(256), 0, st, part, nsplit, ne);
+        hipLaunchKernelGGL(k_direct_fold, dim3((unsigned)((ne + 255) / 256), (unsigned)P), dim3(256), 0, st, part, nsplit, ne);
     switch (spd_tiles(n)) {
 #define FB_SOLVE(T)                                                                                                     \
     case T:                                                                                                             \
         if (primal)                                                                                                     \
             hipLaunchKernelGGL((k_direct_solve<T, true>), dim3((unsigned)P), dim3(64 * spd_waves(T)), 0, st, part,      \
-                               nsplit * ne, n, nt, pl.ld, s, w, Y, r, scal, NS, coef, x, iscal, status);                \
+                               nsplit * ne, n, pl.ld, s, w, Y, r, scal, NS, coef, x, iscal, status);                \
         else                                                                                                            \
             hipLaunchKernelGGL((k_direct_solve<T, false>), dim3((unsigned)P), dim3(64 * spd_waves(T)), 0, st, part,     \
-                               nsplit * ne, n, nt, pl.ld, s, w, Y, r, scal, NS, coef, x, iscal, status);                \
+                               nsplit * ne, n, pl.ld, s, w, Y, r, scal, NS, coef, x, iscal, status);                \
         break;
         FB_SOLVE(1) FB_SOLVE(2) FB_SOLVE(3) FB_SOLVE(4) FB_SOLVE(5) FB_SOLVE(6) FB_SOLVE(7) FB_SOLVE(8) FB_SOLVE(9)
 #undef FB_SOLVE

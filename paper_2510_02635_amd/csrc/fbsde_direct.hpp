@@ -30,13 +30,13 @@ k_direct_fold(double* __restrict__ part, int nsplit, int64_t n) {
     q[0] = a;
 }
 
-// Factors and solves the system of point blockIdx.x (n unknowns, NT tiles per side in `part`, slice stride
-// already folded: the point's matrix is at p * pstride).  Dual: the right-hand side W^1/2 (Y - Ybar) at the
+// Factors and solves the system of point blockIdx.x (n unknowns, the slices in `part` already folded: the point's matrix
+// is at p * pstride, laid out by gram_index).  Dual: the right-hand side W^1/2 (Y - Ybar) at the
 // level's scale; out: coef[p][j] = s w_j^1/2 c_j and coef[p][M] their sum.  Primal: right-hand side r, the
 // slope goes to x.
 template <int T, bool PRIMAL>
 __global__ void __launch_bounds__(64 * spd_waves(T), spd_occupancy(T))
-k_direct_solve(const double* __restrict__ part, int64_t pstride, int n, int NT, int ld, double s,
+k_direct_solve(const double* __restrict__ part, int64_t pstride, int n, int ld, double s,
                const double* __restrict__ w, const double* __restrict__ Y, const double* __restrict__ r,
                const double* __restrict__ scal, int ns, double* __restrict__ coef, double* __restrict__ x,
                int* __restrict__ iscal, uint32_t* __restrict__ status) {
@@ -65,13 +65,10 @@ k_direct_solve(const double* __restrict__ part, int64_t pstride, int n, int NT, 
     bool good = true;
     if (__syncthreads_or(any)) {
         const int np = spd_pivots(n);
+        const uint32_t last = (uint32_t)(gram_entries(n) - 1);   // the padding reads some entry and takes zero
         good = sys.solve(
-            [&](int i, int j) {
-                const int ti = i >> 4, tj = j >> 4;
-                if (tj >= NT) return 0.0;
-                return A[(ti * NT - ti * (ti - 1) / 2 + tj - ti) * 256 + (i >> 2 & 3) * 64 + (i & 3) * 16 + (j & 15)];
-            },
-            [&](double a, int, int) { return a; }, [&](int i) { return (i < n) ? lam : 1.0; },
+            [&](int i, int j) { return A[min((uint32_t)gram_index(n, i, j), last)]; },
+            [&](double a, int i, int j) { return (max(i, j) < n) ? a : 0.0; }, [&](int i) { return (i < n) ? lam : 1.0; },
             [&](int i) { return bv[i]; }, np, np, sh);
     } else {   // as the CG: no step from zero, also where the cloud has no spread and the system is zero
         for (int i = t; i < 16 * T; i += BS) sh.x[i] = 0.0;

@@ -20,6 +20,14 @@
 namespace fbsde {
 
 constexpr int gram_ntile(int nt) { return nt * (nt + 1) / 2; }
+// The 16 x 16 tiles of an n x n matrix's upper triangle, row by row, without the padding beyond n: the rows of tile
+// row t one after the other, n - 16 t entries each.  At most n^2 entries (whole tiles are 6 kB at n = 17, the square 2.3).
+__host__ __device__ constexpr int gram_row(int n, int t) { return 16 * t * n - 128 * t * (t - 1); }   // where tile row t begins
+__host__ __device__ constexpr int gram_entries(int n) { return gram_row(n, n / 16) + (n % 16) * (n - n / 16 * 16); }
+__device__ __forceinline__ int gram_index(int n, int i, int j) {   // j's tile not left of i's
+    const int t = i >> 4;
+    return gram_row(n, t) + (i & 15) * (n - 16 * t) + j - 16 * t;
+}
 constexpr int GRAM_SLICE = 32;   // a block's slice of the contraction is a multiple of this: 16 indices a part
 
 // What is multiplied:
@@ -122,12 +130,11 @@ __device__ __forceinline__ void gram_part(const S* __restrict__ Wp, int64_t ldw,
     }
 }
 
-// Grid (slices, P).  out: DUAL and PRIMAL [P][slices][tiles][256] (tiles of the upper triangle by rows, row-major
-// inside), PLAIN [slices][P][M][M], the upper triangle's tiles only unless there is but one slice, and rsum
-// [slices][P][M].
+// Grid (slices, P).  out: DUAL and PRIMAL [P][slices][gram_entries(n)] (n = M, d), PLAIN [slices][P][M][M], the upper
+// triangle's tiles only unless there is but one slice, and rsum [slices][P][M].
 template <typename S, int NT, int KIND>
 __global__ void __launch_bounds__(256, 2)
-k_gram(const S* __restrict__ W, int64_t ldw, int M, int ld, int slice, double s, const double* __restrict__ Wbar,
+k_gram(const S* __restrict__ W, int64_t ldw, int M, int ld, int n, int slice, double s, const double* __restrict__ Wbar,
        const double* __restrict__ w, double* __restrict__ out, double* __restrict__ rsum) {
     constexpr int NTILE = gram_ntile(NT), TH = NTILE / 2, TM = NTILE - TH;
     constexpr int CH = TM < 6 ? TM : 6;   // tiles of each half a round of the reduction takes
@@ -172,7 +179,7 @@ k_gram(const S* __restrict__ W, int64_t ldw, int M, int ld, int slice, double s,
         }
     }
     double* po = (KIND == GRAM_PLAIN) ? out + ((int64_t)blockIdx.x * gridDim.y + p) * M * M
-                                      : out + ((int64_t)p * gridDim.x + blockIdx.x) * NTILE * 256;
+                                      : out + ((int64_t)p * gridDim.x + blockIdx.x) * gram_entries(n);
 #pragma unroll
     for (int q0 = 0; q0 < TM; q0 += CH) {
         if (q0) __syncthreads();   // the tiles before have been read
@@ -188,16 +195,15 @@ k_gram(const S* __restrict__ W, int64_t ldw, int M, int ld, int slice, double s,
         }
         auto put = [&](int q, int slot) {   // tile q, element t
             const double v = red[0][slot][t] + red[1][slot][t];
-            if constexpr (KIND == GRAM_PRIMAL) po[q * 256 + t] = v;
+            int ti = 0, tj = q;
+            while (tj >= NT) { ++ti; tj += ti - NT; }
+            const int i = 16 * ti + (t >> 4), j = 16 * tj + (t & 15);
+            if (i >= n || j >= n) return;
+            if constexpr (KIND == GRAM_PRIMAL) po[gram_index(n, i, j)] = v;
+            else if constexpr (KIND == GRAM_DUAL) po[gram_index(n, i, j)] = f[i] * f[j] * v;
             else {
-                int ti = 0, tj = q;
-                while (tj >= NT) { ++ti; tj += ti - NT; }
-                const int i = 16 * ti + (t >> 4), j = 16 * tj + (t & 15);
-                if constexpr (KIND == GRAM_DUAL) po[q * 256 + t] = f[i] * f[j] * v;
-                else if (i < M && j < M) {
-                    po[(int64_t)i * M + j] = v;
-                    if (gridDim.x == 1 && ti != tj) po[(int64_t)j * M + i] = v;   // no sum over slices follows
-                }
+                po[(int64_t)i * n + j] = v;
+                if (gridDim.x == 1 && ti != tj) po[(int64_t)j * n + i] = v;   // no sum over slices follows
             }
         };
 #pragma unroll

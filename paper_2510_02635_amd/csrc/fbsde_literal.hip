@@ -579,7 +579,7 @@ void gram_rows(int64_t P, int M, const double* X, int ld, const GramSplit& gs, c
 #define LIT_GRAM(NT)                                                                                                   \
     case NT:                                                                                                           \
         hipLaunchKernelGGL((k_gram<double, NT, GRAM_PLAIN>), dim3(gs.nsplit, (unsigned)P), dim3(256), 0, st, X,        \
-                           (int64_t)ld, M, ld, gs.chunk, 1.0, nullptr, nullptr, w.Gpart, w.Rpart);                     \
+                           (int64_t)ld, M, ld, M, gs.chunk, 1.0, nullptr, nullptr, w.Gpart, w.Rpart);                     \
         break;
         LIT_GRAM(1) LIT_GRAM(2) LIT_GRAM(3) LIT_GRAM(4) LIT_GRAM(5) LIT_GRAM(6) LIT_GRAM(7) LIT_GRAM(8)
 #undef LIT_GRAM
