@@ -47,18 +47,22 @@
 namespace fbsde {
 
 constexpr int CG_FAN = 8;                  // arrival-tree fan-in
-// Polls of its own ticket before a block looks for items elsewhere, about 0.1 ms.  A block that has taken someone
+// A block looks for items elsewhere once it has waited for its own ticket longer than 0.1 ms (wait_ticks, two
+// seconds, over CG_STEAL_PART) and CG_STEAL_ITEMS times what its last item took.  A block that has taken someone
 // else's item is away when its own ticket fills, and nobody else may take that: its point then waits for a whole
-// chunk.  Stealing from the fourth poll on did that to every iteration whose items were not a whole number of
-// rounds over the blocks (three levels at d = 1000, M = 4096, 16 points: 24.2 -> 8.3 ms; d = 700, M = 2100, 40
-// points 43.8 -> 6.5 ms; 1024 points 176 -> 175 ms).  It is there for the queues of blocks that are not resident.
-constexpr int CG_STEAL_AFTER = 64;
+// chunk, whose waiting blocks steal in turn.  So the wait has to be longer than the ordinary one, from the block's
+// last item of an iteration to its first of the next: the rest of the round, as long as an item, and the CG step.
+// Two levels, after the fourth poll, after 64 polls (some 30 us) and now: d = 1000, M = 4096, 16 points 17.3, 5.0,
+// 3.9 ms; d = 5544, M = 2965, 7 points 75, 56, 17; d = 3232, M = 1987, 7 points, FP64 141, 92, 29; d = 7013, M = 5362,
+// 5 points 111, 94, 52 (without the item's share 78).  It is there for the queues of blocks that are not resident
+// and for the level's end, when few points iterate.
+constexpr int CG_STEAL_PART = 20000;
+constexpr int CG_STEAL_ITEMS = 2;
 enum { ST_WAIT_LIMIT = 8 };                // status bit: a bounded device-side wait gave up
 
 // Control words of the device loop, in the workspace: the particle rows streamed by products since the
 // last reset (algorithmic work for measurement), an error flag, and per queue its take and fill counters,
 // each pair on a line of its own.
-constexpr int CG_MAXQ = 32;
 struct CgCtl {
     unsigned long long rows;
     unsigned long long bytes;            // the same rows x d x element bytes (algorithmic read traffic)
@@ -358,6 +362,8 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
     __shared__ double lds[(G::TPW > 1) ? G::TPW * 4 * Q * G::TL : 1];
     __shared__ double red[2 * G::BS / 64 + 16];
     __shared__ int sh_flag;
+    __shared__ uint64_t sh_taken;      // when the block took its last item (in LDS: no register over the item's rows)
+    if (threadIdx.x == 0) sh_taken = wall_clock64();
     const int team0 = threadIdx.x / G::TL, L0 = threadIdx.x % G::TL;
     const int qi = blockIdx.x % nq;   // home queue
     long long tick = -1;               // the block's ticket on its home queue (wave 0), -1: none
@@ -377,6 +383,7 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
             const int lane = threadIdx.x;
             int item = -1;   // -1: leave
             uint64_t t0 = wall_clock64();
+            const uint64_t since = t0, patience = wait_ticks / CG_STEAL_PART + CG_STEAL_ITEMS * (t0 - sh_taken);
             unsigned long long seen = ~0ull;
             for (int k = 0;; ++k) {
                 if (tick < 0) {
@@ -398,9 +405,9 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
                     break;
                 }
                 if (err != 0) break;
-                // after CG_STEAL_AFTER rounds, every fourth: lane q reads queue q's counters (one round trip for all
+                // out of patience, every fourth round: lane q reads queue q's counters (one round trip for all
                 // queues), then the block claims an unticketed item if there is one, home queue first
-                if (k >= CG_STEAL_AFTER && (k & 3) == 3) {
+                if ((k & 3) == 3 && wall_clock64() - since > patience) {
                     unsigned long long h = 0, tl = 0;
                     if (lane < nq) {
                         h = __hip_atomic_load(&ctl->q[lane][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -460,7 +467,10 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
                 if (k < 16) __builtin_amdgcn_s_sleep(1);
                 else __builtin_amdgcn_s_sleep(4);
             }
-            if (lane == 0) sh_flag = item;
+            if (lane == 0) {
+                sh_flag = item;
+                sh_taken = wall_clock64();
+            }
         }
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(sh_flag);

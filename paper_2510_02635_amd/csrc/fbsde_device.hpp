@@ -13,6 +13,8 @@
 
 namespace fbsde {
 
+constexpr int CG_MAXQ = 32;   // work queues of the CG loop at most; points share them evenly
+
 struct Words4 { uint32_t x, y, z, w; };
 
 __device__ __forceinline__ Words4 philox4x32_10(Words4 c, uint32_t k0, uint32_t k1) {

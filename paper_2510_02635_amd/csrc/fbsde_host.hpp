@@ -96,6 +96,21 @@ inline bool shape_plan(Plan& pl, int team, int nchunk) {
     return true;
 }
 
+// Divisor of the chip's block slots that a CG loop launch from this host thread asks for (1 by default).
+extern thread_local int loop_share;
+
+// Blocks of the CG loop that a compute unit holds at once, by its registers as compiled (k_cg_loop over the state's
+// and the arithmetic's type, groups per lane and team width).
+inline int cg_blocks_per_cu(const Plan& pl, bool r64) {
+    if (pl.BS > 256) return 1;
+    if (pl.Q == 1) return 5;
+    if (pl.esz == 8) return (pl.Q == 2) ? 4 : 2;
+    if (pl.Q == 2) return r64 ? 4 : 5;
+    if (pl.Q == 4) return r64 ? 3 : 4;
+    if (pl.Q == 5) return (pl.TEAM == 1 && !r64) ? 3 : 2;
+    return (pl.TEAM == 2) ? 1 : 2;
+}
+
 inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     pl.d = pb->d; pl.M = pb->M; pl.N = pb->N;
     pl.maxit = std::max(1, (int)pb->cg_maxit);
@@ -127,20 +142,27 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     if (pl.TEAM == 0) return FBSDE_EINVAL;   // d beyond 16384 (FP64) / 32768 (FP32C)
     pl.BS = 64 * std::max(pl.TEAM, 4);
     pl.TPW = pl.BS / (64 * pl.TEAM);
-    // Chunks per point: two work items per block that the CG loop holds on the chip at once (its registers, the
-    // bytes of a row per lane in the main, decide how many: 5, 4 or 2 blocks of 256 threads per compute unit, 1
-    // larger one).  With one item a block nothing covers the CG steps between two iterations; more items cost a
-    // partial vector and an arrival each.  At most 128 chunks a point (beyond, the arrival tree is a level
-    // deeper) unless the call has so few points that 512 items need more, at least four, and 16 rows a chunk (8
-    // on teams of eight waves and more).  Measured, three levels of a solve, before (4096 items, 64 rows above
-    // d = 1000) and now, with the loop's stealing delayed in both: d = 1000, M = 4096, 64 points 15.5 -> 13.6 ms
-    // (FP32C) and 55.1 -> 45.7 ms (FP64), 16 points 8.3 -> 4.2, 256 points 48.4 -> 46.6; d = 700, M = 2100, 40 points
-    // 6.5 -> 5.1; d = 5000, M = 600, 6 points 9.5 -> 4.4; d = 5000, M = 3712, 4 points 54.9 -> 42.3; d = 10^4, M =
-    // 1024, 16 points 15.1 -> 11.6.
-    const int row_bytes = pl.Q * 4 * (int)pl.esz;
-    const int64_t per_cu = (pl.BS > 256) ? 1 : (row_bytes <= 32) ? 5 : (row_bytes <= 64) ? 4 : 2;
+    // Chunks per point, 16 rows each at least (8 on teams of eight waves and more).
+    // Up to CG_MAXQ points, a queue each: one work item per block that the chip holds at once.  A point's next
+    // iteration starts when all its items are done, so a part-empty second round costs as much as a full one, and
+    // smaller items cost a partial vector and an arrival each.  Two levels, two items a block but at most 128 chunks
+    // -> now, stealing as it is: d = 5544, M = 2965, 7 points 17.2 -> 15.8 ms; d = 2279, M = 3589, 5 points, FP64 30.6 ->
+    // 24.6; d = 10^4, M = 1024, 16 points 8.4 -> 7.4; d = 1000, M = 4096, 16 points 3.9 -> 2.95; d = 2718, M = 2778, 25
+    // points 201 -> 183 (before either change 186); d = 300, M = 65536, 3 points 3.08 -> 2.46.  At most 512 (one point,
+    // d = 300, M = 65536, FP64 2.66 ms, with 1024 2.80).
+    // More points share their queues and leave them one by one: two items a block, at most 128 chunks (64 points, d =
+    // 1000, M = 4096: FP32C 9.7 against 9.3 ms with one, FP64 31.4 against 30.6; 150 points, d = 400, M = 900 13.1
+    // against 13.4).
+    // At least four chunks, but no more than 4096 items in all: beyond 1024 points four cost 1.05 to 1.3 times the
+    // time (three levels: d = 200, M = 300, 8192 points 121 ms with one chunk, 137 with four; d = 1000, M = 64, 16384
+    // points 57 and 72) and the partial sums of four (d = 1000, M = 64, 65535 points 38.5 GB and 44.0).
+    const bool r64 = pl.esz == 4 && pb->M <= pb->d + 1;   // FP64 arithmetic on the FP32 state (run_level)
     const int64_t np = std::max<int64_t>(P, 1), min_rows = (pl.TEAM >= 8) ? 8 : 16;
-    int64_t nchunk = std::max<int64_t>({std::min<int64_t>(2 * 256 * per_cu / np, 128), 512 / np, 4});
+    // a batched call's loops take a share of the chip each (8 uneven instances of 4 points, split for the whole chip
+    // 75.9 ms, for the share 60.4)
+    const int64_t held = 256 * (int64_t)cg_blocks_per_cu(pl, r64) / std::max(loop_share, 1);
+    const int64_t per_point = (np <= CG_MAXQ) ? std::min<int64_t>(held / np, 512) : std::min<int64_t>(2 * held / np, 128);
+    int64_t nchunk = std::max<int64_t>(per_point, std::min<int64_t>(4, (4096 + np - 1) / np));
     nchunk = std::max<int64_t>(1, std::min<int64_t>(nchunk, std::min<int64_t>(pb->M / (2 * pl.TPW), pb->M / min_rows)));
     const auto chunks = [&](int64_t n) {
         pl.rows_per_chunk = (int)((pb->M + n - 1) / n);
@@ -247,8 +269,6 @@ void shared_reverse(const fbsde_problem* pb, const Plan& pl1, int k, S* W, const
 void clear_status(uint32_t* status, int64_t P, hipStream_t st);
 // Capture what body enqueues (on the stream it is given) into a graph, as fbsde_graph_capture does.
 int capture_graph(const std::function<int(hipStream_t)>& body, hipStream_t stream, fbsde_graph* out);
-// Divisor of the chip's block slots that a CG loop launch from this host thread asks for (1 by default).
-extern thread_local int loop_share;
 // fbsde_solve for one tile of a batched call; reset_counts = false adds its CG traffic to the count the
 // arena already holds (the per-point form keeps it in the loop control at offset 0 of the workspace).
 int solve_tile(const fbsde_problem* pb, int64_t P, const double* x0, double* u, double* grad, uint32_t* status,
