@@ -140,9 +140,9 @@ typedef struct fbsde_problem {
  *     (W^1/2 D' D'^T W^1/2 + lambda I) c = W^1/2 (Y - Ybar), alpha_x = D'^T W^1/2 c (the push-through
  *     identity of the normal equations, Sec. 2.4's system in its dual form);
  *   primal (M > d + 1, d <= 128, cg_maxit >= d, ridge_rel >= 1e-8): Sec. 2.4's d x d system itself;
- * factored by Cholesky.  Every other level, and every level with FBSDE_SOLVER_CG, runs the matrix-free CG;
- * so does a primal level whose workspace has no room for the d x d systems.  The reverse mode always runs
- * CG. */
+ * factored by Cholesky (a zero right-hand side has the zero slope).  Every other level, and every level with
+ * FBSDE_SOLVER_CG, runs the matrix-free CG; so does a primal level whose workspace has no room for the d x d
+ * systems.  The reverse mode always runs CG. */
 enum { FBSDE_SOLVER_AUTO = 0, FBSDE_SOLVER_CG = 1 };
 #define FBSDE_DUAL_MAXM 128
 
@@ -151,7 +151,11 @@ enum { FBSDE_SOLVER_AUTO = 0, FBSDE_SOLVER_CG = 1 };
 int64_t fbsde_state_ld(const fbsde_problem* pb);
 
 /* Workspace bytes needed by fbsde_solve / fbsde_solve_step / fbsde_solve_backward for P
- * points.  flags: FBSDE_WS_TAPE to keep what fbsde_solve_backward needs. */
+ * points.  flags: FBSDE_WS_TAPE to keep what fbsde_solve_backward needs.
+ * Every per-point entry point, the batched ones included, also runs in less: with fewer slices of the direct
+ * solves' Gram matrices, the CG in the primal form's place, and fewer work items a point, as far as these go
+ * (FBSDE_ENOSPC below).  Sums are then split differently, so results agree with those of a workspace of the
+ * full size to rounding (or the CG's tolerance) and not in every bit. */
 int fbsde_workspace_size(const fbsde_problem* pb, int64_t P, int32_t flags, size_t* bytes);
 
 /* Forward half of Algorithm 1 for P points (its first two loops): simulate the Brownian

@@ -142,8 +142,9 @@ struct WS {
 
 // Carve the workspace (base == nullptr: only count).  Returns bytes.  The loop control comes first and
 // the buffers whose size depends on the chunk count (partials, arrival counters) last, so that the tape
-// keeps its place whatever launch shape a later call takes.
-size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
+// keeps its place whatever launch shape a later call takes.  Before those come the caller's own `extra` bytes, at
+// *extra_at.
+size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws, size_t extra = 0, char** extra_at = nullptr) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> char* {
         char* p = base ? base + off : nullptr;
@@ -182,6 +183,8 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
         ws.cbar = (double*)take(PM * 8);
         ws.adj = (double*)take((size_t)P * 16 * 8);
     }
+    char* const at = take(extra);
+    if (extra_at) *extra_at = at;
     // From here on: the CG's buffers, which a direct solve does not use between the end of the moments and its own,
     // so its Gram matrices lie over them.
     const size_t cg_at = off;
@@ -214,14 +217,14 @@ size_t carve(const Plan& pl, int64_t P, int flags, char* base, WS& ws) {
 // slices of them, then the CG in the primal form's place (it needs none; a dual form's one slice and its coefficients
 // take at most M (M + 1) + 1 doubles a point).  Otherwise fewer chunks per point (a partial vector each), down to the
 // plan's least.  Returns whether it fits.
-bool fit_plan(Plan& pl, int64_t P, int flags, size_t bytes) {
+bool fit_plan(Plan& pl, int64_t P, int flags, size_t bytes, size_t extra = 0) {
     WS ws;
     for (;;) {
-        const size_t need = carve(pl, P, flags, nullptr, ws);
+        const size_t need = carve(pl, P, flags, nullptr, ws, extra);
         if (need <= bytes) return true;
         Plan cg = pl;
         cg.direct = DIRECT_NONE;
-        if (need > carve(cg, P, flags, nullptr, ws)) {
+        if (need > carve(cg, P, flags, nullptr, ws, extra)) {
             if (pl.dsplit > 1) pl.dsplit = (pl.dsplit + 1) / 2;
             else if (pl.direct == DIRECT_PRIMAL) pl.direct = DIRECT_NONE;
             else return false;
@@ -993,6 +996,14 @@ size_t per_point_workspace_bytes(const fbsde_problem* pb, int64_t P, int32_t fla
     return carve(pl, P, flags, nullptr, ws);
 }
 
+size_t per_point_least_bytes(const fbsde_problem* pb, int64_t P, int32_t flags) {
+    Plan pl;
+    if (check_problem(pb, P) != FBSDE_OK || make_plan(pb, P, pl) != FBSDE_OK) return 0;
+    (void)fit_plan(pl, P, flags, 0);
+    WS ws;
+    return carve(pl, P, flags, nullptr, ws);
+}
+
 int solve_per_point_terminal(const fbsde_problem* pb, int64_t P, const double* x0, double* u, double* grad,
                              uint32_t* status, void* wsp, size_t ws_bytes, int32_t flags, int32_t* cg_iters_out,
                              hipStream_t st, const TerminalStep& terminal) {
@@ -1016,7 +1027,7 @@ int solve_per_point_terminal(const fbsde_problem* pb, int64_t P, const double* x
 }  // namespace fbsde
 
 namespace {
-// After the per-point workspace: the table V[p][k], k = 0..N, and with the tape the reverse mode's buffers
+// In the per-point workspace, after the tape: the table V[p][k], k = 0..N, and with the tape the reverse mode's buffers
 // (CoefAdj).  base == nullptr: only count.  Returns bytes.
 size_t coef_r_extra(const Plan& pl, int64_t P, int32_t flags, char* base, double** V, CoefAdj* ca) {
     size_t off = 0;
@@ -1083,7 +1094,7 @@ int fbsde_coef_workspace_size(const fbsde_problem* pb, const fbsde_coef* coef, i
     WS ws;
     double* V = nullptr;
     CoefAdj ca{};
-    *bytes = carve(pl, P, flags, nullptr, ws) + coef_r_extra(pl, P, flags, nullptr, &V, &ca);
+    *bytes = carve(pl, P, flags, nullptr, ws, coef_r_extra(pl, P, flags, nullptr, &V, &ca));
     return FBSDE_OK;
 }
 
@@ -1105,10 +1116,11 @@ int fbsde_solve_coef(const fbsde_problem* pb, const fbsde_coef* coef, int64_t P,
     WS ws;
     double* V = nullptr;
     CoefAdj ca{};
-    const size_t base = carve(pl, P, flags, nullptr, ws);
-    if (base + coef_r_extra(pl, P, flags, nullptr, &V, &ca) > ws_bytes) return FBSDE_ENOSPC;
-    carve(pl, P, flags, (char*)wsp, ws);
-    coef_r_extra(pl, P, flags, (char*)wsp + base, &V, &ca);
+    const size_t extra = coef_r_extra(pl, P, flags, nullptr, &V, &ca);
+    if (!fit_plan(pl, P, flags, ws_bytes, extra)) return FBSDE_ENOSPC;
+    char* at = nullptr;
+    carve(pl, P, flags, (char*)wsp, ws, extra, &at);
+    coef_r_extra(pl, P, flags, at, &V, &ca);
     std::vector<double> A, B;
     coef_mean_path(pl, cf, A, B);
     const bool tape = (flags & FBSDE_WS_TAPE) != 0;
@@ -1146,10 +1158,11 @@ int fbsde_solve_coef_backward(const fbsde_problem* pb, const fbsde_coef* coef, i
     WS ws;
     double* V = nullptr;
     CoefAdj ca{};
-    const size_t base = carve(pl, P, FBSDE_WS_TAPE, nullptr, ws);
-    if (base + coef_r_extra(pl, P, FBSDE_WS_TAPE, nullptr, &V, &ca) > ws_bytes) return FBSDE_ENOSPC;
-    carve(pl, P, FBSDE_WS_TAPE, (char*)wsp, ws);
-    coef_r_extra(pl, P, FBSDE_WS_TAPE, (char*)wsp + base, &V, &ca);
+    const size_t extra = coef_r_extra(pl, P, FBSDE_WS_TAPE, nullptr, &V, &ca);
+    if (!fit_plan(pl, P, FBSDE_WS_TAPE, ws_bytes, extra)) return FBSDE_ENOSPC;
+    char* at = nullptr;
+    carve(pl, P, FBSDE_WS_TAPE, (char*)wsp, ws, extra, &at);
+    coef_r_extra(pl, P, FBSDE_WS_TAPE, at, &V, &ca);
     int tag = 0;
     if (hipMemcpyAsync(&tag, ws.tag, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
@@ -1371,7 +1384,7 @@ int fbsde_autotune(const fbsde_problem* pb, int64_t P, const double* x0, void* w
     Plan p0;
     if ((rc = make_plan(pb, P, p0))) return rc;
     WS ws;
-    if (carve(p0, P, 0, nullptr, ws) > ws_bytes) return FBSDE_ENOSPC;
+    if (!fit_plan(p0, P, 0, ws_bytes)) return FBSDE_ENOSPC;
     carve(p0, P, 0, (char*)wsp, ws);
     hipStream_t st = (hipStream_t)stream;
     // a state to time on: the forward sweep of these points; zero weights, direction and scalars
@@ -1574,7 +1587,7 @@ int fbsde_graph_capture(const fbsde_problem* pb, int64_t P, const double* x0, do
     if (!x0 || !u || !status || !ws || P < 1) return FBSDE_EINVAL;
     size_t need = 0;
     if ((rc = fbsde_workspace_size(pb, P, flags, &need))) return rc;
-    if (need > ws_bytes) return FBSDE_ENOSPC;
+    if (need > ws_bytes && (pb->shared_dw || host::per_point_least_bytes(pb, P, flags) > ws_bytes)) return FBSDE_ENOSPC;
     return capture_graph([&](hipStream_t cap) {
         return fbsde_solve(pb, P, x0, u, grad, status, ws, ws_bytes, flags, nullptr, (fbsde_stream)cap);
     }, (hipStream_t)stream, out);

@@ -212,6 +212,25 @@ int tiled_size(const fbsde_problem* pbs, int64_t n_inst, const int64_t* P, const
     return FBSDE_OK;
 }
 
+// The tiles, arenas and streams of a call with a workspace of ws_bytes: smaller arenas than planned where it has no
+// room for them, if every tile runs in them.
+int tiled_fit(const fbsde_problem* pbs, int64_t n_inst, const int64_t* P, const Opts& o, int32_t flags, size_t ws_bytes,
+              std::vector<TileUnit>& units, size_t& arena, int& nw) {
+    size_t need = 0;
+    int rc = tiled_size(pbs, n_inst, P, o, flags, &need, &units, &arena, &nw);
+    if (rc || need <= ws_bytes) return rc;
+    const size_t head = tiled_header_bytes(units.size());
+    if (ws_bytes < head) return FBSDE_ENOSPC;
+    arena = (ws_bytes - head) / (size_t)nw / 256 * 256;
+    for (const TileUnit& t : units) {
+        size_t b = 0;
+        if (!pbs[t.inst].shared_dw) b = per_point_least_bytes(&pbs[t.inst], t.np, flags);
+        else if ((rc = fbsde_workspace_size(&pbs[t.inst], t.np, flags, &b))) return rc;
+        if (b > arena) return FBSDE_ENOSPC;
+    }
+    return FBSDE_OK;
+}
+
 // Parameter adjoints of an instance: the sum of its tiles' sums, in tile order.  The tile indices come
 // as a kernel argument (so a captured graph holds them): up to TILE_LIST per launch, later launches of
 // the same instance adding to the first.
@@ -278,11 +297,10 @@ int run_tiled(const TiledArgs& a, int64_t n_inst, const int64_t* P, const Opts& 
               size_t ws_bytes, hipStream_t caller) {
     const int32_t flags = adjoint ? FBSDE_WS_TAPE : 0;
     std::vector<TileUnit> units;
-    size_t need = 0, arena = 0;
+    size_t arena = 0;
     int nw = 1;
-    int rc = tiled_size(a.pbs, n_inst, P, o, flags, &need, &units, &arena, &nw);
+    int rc = tiled_fit(a.pbs, n_inst, P, o, flags, ws_bytes, units, arena, nw);
     if (rc) return rc;
-    if (need > ws_bytes) return FBSDE_ENOSPC;
     if (units.empty()) {   // every instance is empty: its parameter adjoints are zero sums
         if (adjoint)
             for (int64_t i = 0; i < n_inst; ++i)
@@ -526,9 +544,10 @@ int fbsde_graph_capture_batched(const fbsde_problem* pbs, int64_t n_inst, const 
             std::getenv("FBSDE_CG_HOST_LOOP")[0] == '1')
             return FBSDE_EINVAL;
     }
-    size_t need = 0;
-    if ((rc = tiled_size(pbs, n_inst, P, o, 0, &need))) return rc;
-    if (need > ws_bytes) return FBSDE_ENOSPC;
+    std::vector<TileUnit> units;
+    size_t arena = 0;
+    int nw = 1;
+    if ((rc = tiled_fit(pbs, n_inst, P, o, 0, ws_bytes, units, arena, nw))) return rc;
     TiledArgs a{pbs, x0, u, grad, status, nullptr, nullptr, nullptr, nullptr};
     return capture_graph([&](hipStream_t cap) { return run_tiled(a, n_inst, P, o, false, wsp, ws_bytes, cap); },
                          (hipStream_t)stream, out);

@@ -286,6 +286,8 @@ void set_int(int* a, int v, hipStream_t st);
 // per_point_workspace_bytes is its workspace.
 using TerminalStep = std::function<int(const void* W, int64_t ldw, double* Y, hipStream_t)>;
 size_t per_point_workspace_bytes(const fbsde_problem* pb, int64_t P, int32_t flags);
+// The least it runs in, with fewer work items and Gram slices (fit_plan).
+size_t per_point_least_bytes(const fbsde_problem* pb, int64_t P, int32_t flags);
 int solve_per_point_terminal(const fbsde_problem* pb, int64_t P, const double* x0, double* u, double* grad,
                              uint32_t* status, void* ws, size_t ws_bytes, int32_t flags, int32_t* cg_iters_out,
                              hipStream_t st, const TerminalStep& terminal);

@@ -11,6 +11,8 @@
 #include "fbsde_host.hpp"
 #include "fbsde_mfma.hpp"
 
+#include <cstdint>
+
 using namespace fbsde;
 using namespace fbsde::host;
 
@@ -33,7 +35,10 @@ struct SigmaLayout {
 
 inline size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
-int sigma_layout(const fbsde_problem* pb, int64_t P, int32_t flags, fbsde_problem& pbc, SigmaLayout& L) {
+// For a workspace of ws_bytes: where it is smaller than the whole, the per-point part takes what the other buffers,
+// scratch of one call each, leave, if that part runs in it (total stays above ws_bytes otherwise).
+int sigma_layout(const fbsde_problem* pb, int64_t P, int32_t flags, fbsde_problem& pbc, SigmaLayout& L,
+                 size_t ws_bytes = SIZE_MAX) {
     int rc = check_problem(pb, P);
     if (rc) return rc;
     if (flags & ~FBSDE_WS_TAPE) return FBSDE_EINVAL;
@@ -46,19 +51,27 @@ int sigma_layout(const fbsde_problem* pb, int64_t P, int32_t flags, fbsde_proble
     const size_t esz = (pb->prec == FBSDE_F64) ? 8 : 4;
     const int64_t row_bytes = (int64_t)pb->M * pb->d * (int64_t)esz;
     L.pc = std::max<int64_t>(1, std::min<int64_t>(std::max<int64_t>(P, 1), SIGMA_CHUNK_BYTES / row_bytes));
+    const size_t sig_b = up256((size_t)pb->d * pb->d * esz), t_b = up256((size_t)L.pc * row_bytes),
+                 k_b = up256((size_t)pb->d * pb->d * 8), r_b = up256((size_t)std::max<int64_t>(P, 1) * pb->d * 8),
+                 q_b = (flags & FBSDE_WS_TAPE) ? up256((size_t)std::max<int64_t>(P, 1) * pb->M * 8) : 0;
+    const size_t others = sig_b + t_b + k_b + r_b + 256 + q_b;
+    if (ws_bytes < up256(L.base) + others && ws_bytes >= others) {
+        const size_t left = (ws_bytes - others) / 256 * 256;
+        if (left >= per_point_least_bytes(&pbc, P, flags)) L.base = left;
+    }
     size_t off = up256(L.base);
     L.sig_off = off;
-    off += up256((size_t)pb->d * pb->d * esz);
+    off += sig_b;
     L.t_off = off;
-    off += up256((size_t)L.pc * row_bytes);
+    off += t_b;
     L.k_off = off;
-    off += up256((size_t)pb->d * pb->d * 8);
+    off += k_b;
     L.r_off = off;
-    off += up256((size_t)std::max<int64_t>(P, 1) * pb->d * 8);
+    off += r_b;
     L.info_off = off;
     off += 256;
     L.q_off = off;
-    if (flags & FBSDE_WS_TAPE) off += up256((size_t)std::max<int64_t>(P, 1) * pb->M * 8);
+    off += q_b;
     L.total = off;
     return FBSDE_OK;
 }
@@ -170,7 +183,7 @@ int fbsde_solve_sigma(const fbsde_problem* pb, const double* sigma, int64_t P, c
                       int32_t* cg_iters_out, fbsde_stream stream) {
     fbsde_problem pbc;
     SigmaLayout L;
-    int rc = sigma_layout(pb, P, flags, pbc, L);
+    int rc = sigma_layout(pb, P, flags, pbc, L, ws_bytes);
     if (rc) return rc;
     if (P == 0) {
         if (cg_iters_out)
@@ -214,7 +227,7 @@ int fbsde_solve_sigma_backward(const fbsde_problem* pb, const double* sigma, int
                                void* wsp, size_t ws_bytes, int32_t* cg_iters_out, fbsde_stream stream) {
     fbsde_problem pbc;
     SigmaLayout L;
-    int rc = sigma_layout(pb, P, FBSDE_WS_TAPE, pbc, L);
+    int rc = sigma_layout(pb, P, FBSDE_WS_TAPE, pbc, L, ws_bytes);
     if (rc) return rc;
     if (!gp_bar || !fp_bar) return FBSDE_EINVAL;
     if (P > 0 && (!sigma || !wsp)) return FBSDE_EINVAL;
