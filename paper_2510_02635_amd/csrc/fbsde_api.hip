@@ -402,6 +402,28 @@ int point_iters_max(const WS& ws, int64_t P, hipStream_t st, int& err) {
     return m;
 }
 
+// A rank-deficient design (M <= d + 1) in FP32C: FP64 arithmetic on the FP32 state in the moments and the CG product,
+// whose FP32 rounding would otherwise reach the ridge-only null space of the design (where the solution carries it
+// with weight 1/lam).
+template <typename S>
+bool fp64_on_fp32(const Plan& pl) { return !std::is_same<S, double>::value && pl.M <= pl.d + 1; }
+
+template <typename S>
+void launch_moments(const Plan& pl, int64_t P, const S* W, int64_t ldw, const double* w, const double* xw, const WS& ws,
+                    int warm, hipStream_t st) {
+    dispatch_rows<S>(pl, [&](auto qc, auto tc) {
+        constexpr int QQ = decltype(qc)::value, TT = decltype(tc)::value;
+        auto go = [&](auto arith) {
+            using R = decltype(arith);
+            hipLaunchKernelGGL((k_moments<S, R, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS), 0, st, W,
+                               ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w, ws.c2, xw, ws.scal, NS, warm,
+                               ws.part1, ws.part2, ws.part3, ws.psc);
+        };
+        if (fp64_on_fp32<S>(pl)) go(double{});
+        else go(S{});
+    });
+}
+
 // One backward level: regression of Y_next on the cloud W (at t_{k+1}); leaves alpha_x in ws.x,
 // alpha / zz in ws.scal, and returns the number of CG iterations.
 template <typename S>
@@ -419,25 +441,12 @@ int run_level(const fbsde_problem* pb, const Plan& pl, int64_t P, int k, const S
     const int vstride = (int)pl.N + 1;
     hipLaunchKernelGGL(k_weights, dim3((unsigned)P), dim3(256), 0, st, rn2, Y_next, (int)pl.M, s2, eps2, w_out,
                        ws.c2, ws.scal, NS, ws.active, (int)P, warm, vt, vstride, pb->eps_h * pb->eps_h);
-    // a rank-deficient design (M <= d + 1) in FP32C: FP64 arithmetic on the FP32 state in the moments and
-    // the CG product, whose FP32 rounding would otherwise reach the ridge-only null space of the design
-    // (where the solution carries it with weight 1/lam)
-    const bool r64 = !std::is_same<S, double>::value && pl.M <= pl.d + 1;
+    const bool r64 = fp64_on_fp32<S>(pl);
     // the warm start's direction goes from level to level in qv, which only the CG uses in between, and the scaled
     // slope before it in part2, which only the moments use
     const bool ext = !pl.direct && pl.M >= 2 * pl.d;
     const double* xw = ext ? ws.qv : ws.x;
-    dispatch_rows<S>(pl, [&](auto qc, auto tc) {
-        constexpr int QQ = decltype(qc)::value, TT = decltype(tc)::value;
-        if (r64)
-            hipLaunchKernelGGL((k_moments<S, double, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS), 0,
-                               st, W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w_out, ws.c2, xw, ws.scal,
-                               NS, warm, ws.part1, ws.part2, ws.part3, ws.psc);
-        else
-            hipLaunchKernelGGL((k_moments<S, S, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS), 0, st,
-                               W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, w_out, ws.c2, xw, ws.scal, NS,
-                               warm, ws.part1, ws.part2, ws.part3, ws.psc);
-    });
+    launch_moments<S>(pl, P, W, ldw, w_out, xw, ws, warm, st);
     const int vc = fold_parts(pl, P, ws.part1, ws.part2, warm ? ws.part3 : nullptr, st);
     hipLaunchKernelGGL(k_moments_finish, dim3((unsigned)P), dim3(256), 0, st, ws.part1, ws.part2, ws.part3, ws.psc,
                        pl.nchunk, vc, pl.ld, pb->s, lam, warm, Wbar_out, ws.x, xw, ext ? 1 : 0, ws.r, ws.pv, ws.scal, NS, ws.iscal,
@@ -1332,9 +1341,14 @@ int fbsde_time_kernel(const fbsde_problem* pb, int64_t P, int32_t which, int32_t
             if (which == 0) {
                 dispatch<S>(pl.Q, pl.TEAM, [&](auto qc, auto tc) {
                     constexpr int QQ = decltype(qc)::value, TT = decltype(tc)::value;
-                    hipLaunchKernelGGL((k_matvec<S, S, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS),
-                                       0, st, W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, pb->s, ws.w,
-                                       ws.pv, ws.scal, NS, ws.iscal, ws.part1, ws.psc);
+                    auto go = [&](auto arith) {
+                        using R = decltype(arith);
+                        hipLaunchKernelGGL((k_matvec<S, R, QQ, TT>), dim3(pl.nchunk, (unsigned)P),
+                                           dim3(Geo<QQ, TT>::BS), 0, st, W, ldw, (int)pl.M, pl.rows_per_chunk,
+                                           pl.nchunk, pl.ld, pb->s, ws.w, ws.pv, ws.scal, NS, ws.iscal, ws.part1, ws.psc);
+                    };
+                    if (fp64_on_fp32<S>(pl)) go(double{});
+                    else go(S{});
                 });
             } else if (which == 1) {
                 launch_reverse<S>(pb, pl, P, 1, W, ldw, ws.x, ws, ws.Yb, ws.rn2, (uint32_t*)ws.iscal, st);
@@ -1347,12 +1361,8 @@ int fbsde_time_kernel(const fbsde_problem* pb, int64_t P, int32_t which, int32_t
                 hipLaunchKernelGGL(k_stream_read, dim3(blocks), dim3(256), 0, st, (const uint4*)W, n16,
                                    (uint32_t*)ws.part1);
             } else if (which == 2) {
-                dispatch<S>(pl.Q, pl.TEAM, [&](auto qc, auto tc) {
-                    constexpr int QQ = decltype(qc)::value, TT = decltype(tc)::value;
-                    hipLaunchKernelGGL((k_moments<S, S, QQ, TT>), dim3(pl.nchunk, (unsigned)P), dim3(Geo<QQ, TT>::BS),
-                                       0, st, W, ldw, (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, ws.w, ws.c2,
-                                       ws.x, ws.scal, NS, 1, ws.part1, ws.part2, ws.part3, ws.psc);
-                });
+                // as in the solve's levels, which have a warm start's product with the CG on full-rank designs only
+                launch_moments<S>(pl, P, W, ldw, ws.w, ws.x, ws, (!pl.direct && pl.M > pl.d + 1) ? 1 : 0, st);
             } else {
                 // the evaluation points of this timing run: the [P][ld] >= [P][d] scratch vector
                 launch_forward<S>(pb, pl, P, ws.Wbar, W, ldw, ws.Yb, ws.rn2, (uint32_t*)ws.iscal, st);
