@@ -318,6 +318,8 @@ int run_cg_device(const fbsde_problem* pb, const Plan& pl, int64_t P, const S* W
         return 0;
     }
     const uint64_t wait_ticks = (uint64_t)std::max(khz, 1000) * 2000ull;
+    const bool shares = loop_share > 1;
+    const uint64_t steal_ticks = (uint64_t)std::max(khz, 1000) * (shares ? CG_STEAL_SHARED_US : CG_STEAL_US) / 1000;
     const int64_t ncnt_total = P * (int64_t)ws.ncnt, nitems = P * (int64_t)pl.nchunk;
     const int64_t nslots = ws.nq * ws.qcap;
     hipLaunchKernelGGL(k_cg_arm,
@@ -337,7 +339,7 @@ int run_cg_device(const fbsde_problem* pb, const Plan& pl, int64_t P, const S* W
                            (int)pl.M, pl.rows_per_chunk, pl.nchunk, pl.ld, pb->s, w, Wbar, ws.x, ws.r, ws.pv, ws.qv,
                            ws.scal, NS, ws.iscal, ws.part1, ws.psc, ws.ctl, ws.queue, ws.nq, ws.qcap, ws.active,
                            ws.cnt, ws.ncnt, cg_rtol_of(pb) * cg_rtol_of(pb), std::min(cap, pb->cg_maxit), status,
-                           wait_ticks);
+                           wait_ticks, steal_ticks, shares ? 0 : CG_STEAL_ITEMS);
         lt_end(tl, st);
     });
     hipLaunchKernelGGL(k_cg_check, dim3((unsigned)std::min<int64_t>((P + 255) / 256, 1024)), dim3(256), 0, st,

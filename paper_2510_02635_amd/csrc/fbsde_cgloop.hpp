@@ -47,17 +47,18 @@
 namespace fbsde {
 
 constexpr int CG_FAN = 8;                  // arrival-tree fan-in
-// A block looks for items elsewhere once it has waited for its own ticket longer than 0.1 ms (wait_ticks, two
-// seconds, over CG_STEAL_PART) and CG_STEAL_ITEMS times what its last item took.  A block that has taken someone
-// else's item is away when its own ticket fills, and nobody else may take that: its point then waits for a whole
-// chunk, whose waiting blocks steal in turn.  So the wait has to be longer than the ordinary one, from the block's
-// last item of an iteration to its first of the next: the rest of the round, as long as an item, and the CG step.
-// Two levels, after the fourth poll, after 64 polls (some 30 us) and now: d = 1000, M = 4096, 16 points 17.3, 5.0,
-// 3.9 ms; d = 5544, M = 2965, 7 points 75, 56, 17; d = 3232, M = 1987, 7 points, FP64 141, 92, 29; d = 7013, M = 5362,
-// 5 points 111, 94, 52 (without the item's share 78).  It is there for the queues of blocks that are not resident
-// and for the level's end, when few points iterate.
-constexpr int CG_STEAL_PART = 20000;
-constexpr int CG_STEAL_ITEMS = 2;
+// A block looks for items elsewhere once it has waited for its own ticket longer than CG_STEAL_US and CG_STEAL_ITEMS
+// times what its last item took.  A block that has taken someone else's item is away when its own ticket fills, and
+// nobody else may take that: its point then waits for a whole chunk, whose waiting blocks steal in turn.  So the wait
+// has to be longer than the ordinary one, from the block's last item of an iteration to its first of the next: the
+// rest of the round, as long as an item, and the CG step.  Two levels, after the fourth poll, after 64 polls (some
+// 30 us) and now: d = 1000, M = 4096, 16 points 17.3, 5.0, 3.9 ms; d = 5544, M = 2965, 7 points 75, 56, 17; d = 3232,
+// M = 1987, 7 points, FP64 141, 92, 29; d = 7013, M = 5362, 5 points 111, 94, 52 (without the item's share 78).  It is
+// there for the queues of blocks that are not resident and for the level's end, when few points iterate.
+// Loops that share the chip (a batched call's streams, half of it each) have two rounds of items where the chip's
+// own plan has one, so that other queues' second rounds are worth taking earlier: 8 uneven instances of 4 points
+// 71.7, 70.8, 72.6, 75.6 ms after 40, 50, 60, 80 us and 76.1 by the rule above; 5 instances 85.2, 83.6, 84.4, 86.8, 86.4.
+constexpr int CG_STEAL_US = 100, CG_STEAL_ITEMS = 2, CG_STEAL_SHARED_US = 50;
 enum { ST_WAIT_LIMIT = 8 };                // status bit: a bounded device-side wait gave up
 
 // Control words of the device loop, in the workspace: the particle rows streamed by products since the
@@ -357,7 +358,7 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
           double* __restrict__ pv, double* __restrict__ qv, double* __restrict__ scal, int ns, int* __restrict__ iscal,
           double* __restrict__ part, double* __restrict__ psc, CgCtl* ctl, unsigned long long* __restrict__ queue,
           int nq, int64_t qcap, int* active, int* __restrict__ cnt, int ncnt, double rtol2, int maxit,
-          uint32_t* __restrict__ status, uint64_t wait_ticks) {
+          uint32_t* __restrict__ status, uint64_t wait_ticks, uint64_t steal_ticks, int steal_items) {
     using G = Geo<Q, TEAM>;
     __shared__ double lds[(G::TPW > 1) ? G::TPW * 4 * Q * G::TL : 1];
     __shared__ double red[2 * G::BS / 64 + 16];
@@ -383,7 +384,7 @@ k_cg_loop(const S* __restrict__ W, int64_t ldw, int M, int rows_per_chunk, int n
             const int lane = threadIdx.x;
             int item = -1;   // -1: leave
             uint64_t t0 = wall_clock64();
-            const uint64_t since = t0, patience = wait_ticks / CG_STEAL_PART + CG_STEAL_ITEMS * (t0 - sh_taken);
+            const uint64_t since = t0, patience = steal_ticks + (uint64_t)steal_items * (t0 - sh_taken);
             unsigned long long seen = ~0ull;
             for (int k = 0;; ++k) {
                 if (tick < 0) {

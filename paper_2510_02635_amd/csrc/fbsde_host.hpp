@@ -96,9 +96,6 @@ inline bool shape_plan(Plan& pl, int team, int nchunk) {
     return true;
 }
 
-// Divisor of the chip's block slots that a CG loop launch from this host thread asks for (1 by default).
-extern thread_local int loop_share;
-
 // Blocks of the CG loop that a compute unit holds at once, by its registers as compiled (k_cg_loop over the state's
 // and the arithmetic's type, groups per lane and team width).
 inline int cg_blocks_per_cu(const Plan& pl, bool r64) {
@@ -158,9 +155,7 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     // points 57 and 72) and the partial sums of four (d = 1000, M = 64, 65535 points 38.5 GB and 44.0).
     const bool r64 = pl.esz == 4 && pb->M <= pb->d + 1;   // FP64 arithmetic on the FP32 state (run_level)
     const int64_t np = std::max<int64_t>(P, 1), min_rows = (pl.TEAM >= 8) ? 8 : 16;
-    // a batched call's loops take a share of the chip each (8 uneven instances of 4 points, split for the whole chip
-    // 75.9 ms, for the share 60.4)
-    const int64_t held = 256 * (int64_t)cg_blocks_per_cu(pl, r64) / std::max(loop_share, 1);
+    const int64_t held = 256 * (int64_t)cg_blocks_per_cu(pl, r64);
     const int64_t per_point = (np <= CG_MAXQ) ? std::min<int64_t>(held / np, 512) : std::min<int64_t>(2 * held / np, 128);
     int64_t nchunk = std::max<int64_t>(per_point, std::min<int64_t>(4, (4096 + np - 1) / np));
     nchunk = std::max<int64_t>(1, std::min<int64_t>(nchunk, std::min<int64_t>(pb->M / (2 * pl.TPW), pb->M / min_rows)));
@@ -269,6 +264,8 @@ void shared_reverse(const fbsde_problem* pb, const Plan& pl1, int k, S* W, const
 void clear_status(uint32_t* status, int64_t P, hipStream_t st);
 // Capture what body enqueues (on the stream it is given) into a graph, as fbsde_graph_capture does.
 int capture_graph(const std::function<int(hipStream_t)>& body, hipStream_t stream, fbsde_graph* out);
+// Divisor of the chip's block slots that a CG loop launch from this host thread asks for (1 by default).
+extern thread_local int loop_share;
 // fbsde_solve for one tile of a batched call; reset_counts = false adds its CG traffic to the count the
 // arena already holds (the per-point form keeps it in the loop control at offset 0 of the workspace).
 int solve_tile(const fbsde_problem* pb, int64_t P, const double* x0, double* u, double* grad, uint32_t* status,
