@@ -401,7 +401,7 @@ def solve_batched(problems, x0s, want_grad=True, mode="tiled", streams=3, tile_b
     """Batched solve of several instances: lists of Problem and of device x0 [P_i][d_i] tensors.
 
     mode "tiled" (point tiles over `streams` concurrent streams, each tile at most `tile_bytes` of
-    workspace, 0 = 8 GiB) or "persistent" (one persistent launch per geometry class, `max_slots`
+    workspace, 0 = 24 GiB) or "persistent" (one persistent launch per geometry class, `max_slots`
     workgroups).  Returns lists (u_i, grad_i or None, status_i).
     """
     n, cps, Ps = _batch_common(problems, x0s)

@@ -132,6 +132,8 @@ int read_opts(const fbsde_batch_opts* o, Opts& r) {
 // centred ridge system of an isotropic cloud: the Marchenko-Pastur edges (1 -+ sqrt(r))^2 with
 // r = min(d, M) / max(d, M), the smallest eigenvalue held above a floor set by the ridge (relative to the
 // spread s^2 t of the cloud); CG reaches a relative residual rtol in about sqrt(kappa) ln(2 / rtol) / 2 iterations.
+// A tile whose levels are solved directly (small d or M) is priced by the CG's iterations as well, so too high: such
+// tiles are small beside the ones that decide how the streams fill.
 double tile_cost(const fbsde_problem& pb, const Plan& pl, int64_t m) {
     const double r = (double)std::min(pb.d, pb.M) / (double)std::max(pb.d, pb.M);
     const double hi = (1.0 + std::sqrt(r)) * (1.0 + std::sqrt(r));

@@ -111,8 +111,11 @@ inline int cg_blocks_per_cu(const Plan& pl, bool r64) {
 inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     pl.d = pb->d; pl.M = pb->M; pl.N = pb->N;
     pl.maxit = std::max(1, (int)pb->cg_maxit);
-    // the direct dual solve where the cloud is small and not much thinner than d: CG iterations grow with
-    // M / d towards the near-square design (measured at M = 100: 157 per level at d = 100, 34 at d = 500)
+    // The direct dual solve where the cloud is small (the Gram kernel holds the tiles of at most 128 rows in registers)
+    // and not much thinner than d.  The line at M = d / 8 was drawn for a solve of one block a point, which was slower
+    // than the CG beyond it; the present one is the faster at every size tried (a level, 64 points, M = 100: FP64 d =
+    // 500 141 against 656 us, d = 1000 186 against 727, d = 4000 455 against 1605; FP32C 133 and 368, 163 and 383, 444
+    // and 736), so nothing would be lost by moving it.
     pl.direct = DIRECT_NONE;
     if (pb->solver == FBSDE_SOLVER_AUTO && !pb->shared_dw && pb->ridge_rel > 0.0 && pb->cg_fixed_iters == 0) {
         if (pb->M <= FBSDE_DUAL_MAXM && pb->M <= pb->d + 1 && 8 * pb->M >= pb->d) pl.direct = DIRECT_DUAL;
