@@ -12,7 +12,7 @@
 // (direct solve) and register blocks on the vector units (literal scheme), per level:
 // literal scheme, 64 points, M = 100, d = 10^4 343 -> 174 us (53 TFLOP/s over the tiles); direct primal, 512 points,
 // M = 1024, d = 100 235 -> 141 us (53 TFLOP/s); direct dual, 64 points, M = 100, d = 500 22 -> 17 us and d = 100 15 -> 13;
-// one point, M = 512, d = 100 10 -> 6.7 us.
+// one point, M = 512, d = 100 10 -> 7 us.
 #pragma once
 #include "fbsde_rowteam.hpp"
 #include "fbsde_spd.hpp"
@@ -85,7 +85,6 @@ __device__ __forceinline__ void gram_part(const S* __restrict__ Wp, int64_t ldw,
 #pragma unroll
                 for (int i = 0; i < NT; ++i) nx[i][e] = r[16 * i];
                 nw[e] = wp[min(j, M - 1)];
-                if (j >= k1) nw[e] = 0.0;
             }
         } else {
 #pragma unroll
@@ -99,7 +98,9 @@ __device__ __forceinline__ void gram_part(const S* __restrict__ Wp, int64_t ldw,
         double x[NT][KE], wk[KE];
 #pragma unroll
         for (int e = 0; e < KE; ++e) {
-            wk[e] = nw[e];
+            // the weight past the slice's end is dropped here and not where it is fetched: used at once, its load keeps
+            // the step's other loads behind it (256 -> 370 us, 8 points, M = 10^5, d = 128)
+            wk[e] = (PRIMAL && kc + 4 * e + g >= k1) ? 0.0 : nw[e];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 if constexpr (PRIMAL) x[i][e] = (double)nx[i][e] - wbc[i];
@@ -198,7 +199,7 @@ k_gram(const S* __restrict__ W, int64_t ldw, int M, int ld, int n, int slice, do
             int ti = 0, tj = q;
             while (tj >= NT) { ++ti; tj += ti - NT; }
             const int i = 16 * ti + (t >> 4), j = 16 * tj + (t & 15);
-            if (i >= n || j >= n) return;
+            if (tj == NT - 1 && (i >= n || j >= n)) return;   // padding, in the last tile column only
             if constexpr (KIND == GRAM_PRIMAL) po[gram_index(n, i, j)] = v;
             else if constexpr (KIND == GRAM_DUAL) po[gram_index(n, i, j)] = f[i] * f[j] * v;
             else {

@@ -159,7 +159,10 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     const bool r64 = pl.esz == 4 && pb->M <= pb->d + 1;   // FP64 arithmetic on the FP32 state (run_level)
     const int64_t np = std::max<int64_t>(P, 1), min_rows = (pl.TEAM >= 8) ? 8 : 16;
     const int64_t held = 256 * (int64_t)cg_blocks_per_cu(pl, r64);
-    const int64_t per_point = (np <= CG_MAXQ) ? std::min<int64_t>(held / np, 512) : std::min<int64_t>(2 * held / np, 128);
+    // Levels solved directly have no CG items, only the moments' and the reversal's rows: as for more points (8 points,
+    // M = 10^5, d = 128: 128 chunks 348 and 168 us, 160 chunks 390 and 185).
+    const int64_t per_point = (np <= CG_MAXQ && !pl.direct) ? std::min<int64_t>(held / np, 512)
+                                                            : std::max<int64_t>(std::min<int64_t>(2 * held / np, 128), 512 / np);
     int64_t nchunk = std::max<int64_t>(per_point, std::min<int64_t>(4, (4096 + np - 1) / np));
     nchunk = std::max<int64_t>(1, std::min<int64_t>(nchunk, std::min<int64_t>(pb->M / (2 * pl.TPW), pb->M / min_rows)));
     const auto chunks = [&](int64_t n) {
