@@ -153,9 +153,10 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     // More points share their queues and leave them one by one: two items a block, at most 128 chunks (64 points, d =
     // 1000, M = 4096: FP32C 9.7 against 9.3 ms with one, FP64 31.4 against 30.6; 150 points, d = 400, M = 900 13.1
     // against 13.4).
-    // At least four chunks, but no more than 4096 items in all: beyond 1024 points four cost 1.05 to 1.3 times the
-    // time (three levels: d = 200, M = 300, 8192 points 121 ms with one chunk, 137 with four; d = 1000, M = 64, 16384
-    // points 57 and 72) and the partial sums of four (d = 1000, M = 64, 65535 points 38.5 GB and 44.0).
+    // At least four chunks, but no more than 4096 items in all and, beyond ld = 1024, of 64 rows: beyond 1024 points
+    // four cost 1.05 to 1.3 times the time (three levels: d = 200, M = 300, 8192 points 121 ms with one chunk, 137 with
+    // four; d = 1000, M = 64, 16384 points 57 and 72) and the partial sums of four (d = 1000, M = 64, 65535 points 38.5 GB
+    // and 44.0); 624 points at d = 3559, M = 182 13.3 ms with two and 13.9 with four.
     const bool r64 = pl.esz == 4 && pb->M <= pb->d + 1;   // FP64 arithmetic on the FP32 state (run_level)
     const int64_t np = std::max<int64_t>(P, 1), min_rows = (pl.TEAM >= 8) ? 8 : 16;
     const int64_t held = 256 * (int64_t)cg_blocks_per_cu(pl, r64);
@@ -163,15 +164,15 @@ inline int make_plan(const fbsde_problem* pb, int64_t P, Plan& pl) {
     // M = 10^5, d = 128: 128 chunks 348 and 168 us, 160 chunks 390 and 185).
     const int64_t per_point = (np <= CG_MAXQ && !pl.direct) ? std::min<int64_t>(held / np, 512)
                                                             : std::max<int64_t>(std::min<int64_t>(2 * held / np, 128), 512 / np);
-    int64_t nchunk = std::max<int64_t>(per_point, std::min<int64_t>(4, (4096 + np - 1) / np));
+    // 4096 items in all, 64 rows a chunk beyond ld = 1024: no more than this is asked of a workspace that is smaller
+    // than the plan's own
+    const int64_t few = std::min<int64_t>({(4096 + np - 1) / np, pb->M / (2 * pl.TPW), pb->M / ((pl.ld <= 1024) ? 16 : 64)});
+    int64_t nchunk = std::max<int64_t>(per_point, std::min<int64_t>(4, few));
     nchunk = std::max<int64_t>(1, std::min<int64_t>(nchunk, std::min<int64_t>(pb->M / (2 * pl.TPW), pb->M / min_rows)));
     const auto chunks = [&](int64_t n) {
         pl.rows_per_chunk = (int)((pb->M + n - 1) / n);
         pl.nchunk = (int)((pb->M + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
     };
-    // 4096 items in all, 64 rows a chunk beyond ld = 1024: no more than this is asked of a workspace that is smaller
-    // than the plan's own
-    const int64_t few = std::min<int64_t>({(4096 + np - 1) / np, pb->M / (2 * pl.TPW), pb->M / ((pl.ld <= 1024) ? 16 : 64)});
     chunks(std::max<int64_t>(1, std::min<int64_t>(nchunk, few)));
     pl.least_chunks = pl.nchunk;
     chunks(nchunk);
